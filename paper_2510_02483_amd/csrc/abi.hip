@@ -214,13 +214,27 @@ ls::AttnShape attn_shape(const Dims& m) {
   return ls::AttnShape{(int)m.B, (int)m.S, (int)m.nq, (int)m.nkv, (int)m.dp, (int)m.d};
 }
 
-// fp32 partial sums of the weight-gradient products that split K (their
-// output tiles alone would leave most compute units idle)
-int64_t max_kpart_floats(std::initializer_list<std::array<int64_t, 3>> shapes) {
+// Floats of fp32 partial sums for the products that split K (their output
+// tiles alone would leave most compute units idle): the most any of the
+// products named needs.  Only what the choice of tile depends on is set.
+ls::GemmArgs product(int epi, bool a_kcontig, bool b_kcontig, int64_t M, int64_t N, int64_t K, int64_t b_start1 = 1 << 30) {
+  ls::GemmArgs g;
+  g.epi = epi;
+  g.a_kcontig = a_kcontig;
+  g.b_kcontig = b_kcontig;
+  g.M = (int)M;
+  g.N = (int)N;
+  g.K = (int)K;
+  g.b_start[1] = (int)b_start1;
+  return g;
+}
+int64_t max_kpart_floats(std::initializer_list<ls::GemmArgs> products) {
   int64_t n = 0;
-  for (const auto& mnk : shapes) n = std::max(n, ls::gemm_kpart_floats((int)mnk[0], (int)mnk[1], (int)mnk[2]));
+  for (const ls::GemmArgs& g : products) n = std::max(n, ls::gemm_kpart_floats(g));
   return n;
 }
+// Columns of the gate/up product: whole 64-feature blocks of gate and up.
+int64_t glu_cols(const Dims& m) { return 2 * ((m.I + 63) / 64) * 64; }
 
 struct AttnWs {
   size_t rope, dO, dqkv, dh1, partial, core, wpad, wopad, gpad, gopad, kpart, total;
@@ -240,7 +254,14 @@ AttnWs attn_ws_layout(const Dims& m) {
   w.dh1 = c.take(m.T * m.H * 2);
   w.partial = c.take(norm_partial_bytes(m));
   w.core = c.take(ls::attn_bwd_workspace(attn_shape(m)));
-  w.kpart_floats = max_kpart_floats({{m.H, m.Pq, m.T}, {m.Pqkv, m.H, m.T}});  // dWo, dWqkv
+  w.kpart_floats = max_kpart_floats({
+      product(ls::EPI_ROPE, true, true, m.T, m.Pqkv, m.H, m.Pq),  // q/k/v projection
+      product(ls::EPI_RESID, true, true, m.T, m.H, m.Pq),         // output projection
+      product(ls::EPI_BF16, true, false, m.T, m.Pq, m.H),         // dO
+      product(ls::EPI_BF16, true, false, m.T, m.H, m.Pqkv),       // dh1
+      product(ls::EPI_F32, false, false, m.H, m.Pq, m.T),         // dWo
+      product(ls::EPI_F32, false, false, m.Pqkv, m.H, m.T),       // dWqkv
+  });
   w.kpart = c.take((size_t)w.kpart_floats * 4);
   w.total = c.off;
   return w;
@@ -256,7 +277,14 @@ MlpWs mlp_ws_layout(const Dims& m) {
   w.dgu = c.take(m.T * 2 * m.I * 2);
   w.dh2 = c.take(m.T * m.H * 2);
   w.partial = c.take(norm_partial_bytes(m));
-  w.kpart_floats = max_kpart_floats({{m.H, m.I, m.T}, {2 * m.I, m.H, m.T}});  // dWd, dWg/dWu
+  w.kpart_floats = max_kpart_floats({
+      product(ls::EPI_GLU_FWD, true, true, m.T, glu_cols(m), m.H),  // gate/up projection
+      product(ls::EPI_RESID, true, true, m.T, m.H, m.I),            // down projection
+      product(ls::EPI_GLU_BWD, true, false, m.T, m.I, m.H),         // dact
+      product(ls::EPI_BF16, true, false, m.T, m.H, 2 * m.I),        // dh2
+      product(ls::EPI_F32, false, false, m.H, m.I, m.T),            // dWd
+      product(ls::EPI_F32, false, false, 2 * m.I, m.H, m.T),        // dWg/dWu
+  });
   w.kpart = c.take((size_t)w.kpart_floats * 4);
   w.total = c.off;
   return w;
@@ -377,6 +405,8 @@ int run_attn_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
   g.seq = (int)m.S;
   g.head_dim = (int)m.dp;
   g.rope_cols = (int)(m.Pq + m.Pkv);
+  g.kpart = at<float>(ws, wl.kpart);
+  g.kpart_floats = wl.kpart_floats;
   LS_STEP("qkv projection", st, ls::gemm(g, st));
   LS_STEP("attention fwd", st, ls::attn_fwd(attn_shape(m), qkv, o, lse, st));
   if (!out_proj) return LS_OK;
@@ -392,6 +422,8 @@ int run_attn_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
   p.R = x;
   p.C = x2;
   p.ldc = m.H;
+  p.kpart = at<float>(ws, wl.kpart);
+  p.kpart_floats = wl.kpart_floats;
   LS_STEP("output projection", st, ls::gemm(p, st));
   return LS_OK;
 }
@@ -428,6 +460,8 @@ int run_attn_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
     g.epi = ls::EPI_BF16;
     g.C = dO;
     g.ldc = m.Pq;
+    g.kpart = at<float>(ws, wl.kpart);
+    g.kpart_floats = wl.kpart_floats;
     LS_STEP("dO", st, ls::gemm(g, st));
   }
   {  // dWo (+)= dx2^T o  (padded layout: into the workspace, then folded back)
@@ -470,6 +504,8 @@ int run_attn_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
     g.epi = ls::EPI_BF16;
     g.C = dh1;
     g.ldc = m.H;
+    g.kpart = at<float>(ws, wl.kpart);
+    g.kpart_floats = wl.kpart_floats;
     LS_STEP("dh1", st, ls::gemm(g, st));
   }
   {  // dWq, dWk, dWv (+)= dqkv^T h1  (padded layout: into the workspace, then folded back)
@@ -517,8 +553,10 @@ int run_attn_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
 // keep_gu = false: a forward pass whose saved state is not used (the backward
 // pass recomputes it) skips writing the gate and up outputs.  down = false:
 // stop before the down projection (a recomputation whose y is already known).
+// kpart: scratch for split products (null: none).
 int run_mlp_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x2, const ls_block_weights* w, bf16_t* y,
-                void* saved, hipStream_t st, bool keep_gu = true, bool down = true) {
+                void* saved, float* kpart, int64_t kpart_floats, hipStream_t st, bool keep_gu = true,
+                bool down = true) {
   const MlpSaved sv = mlp_saved_layout(m);
   bf16_t* h2 = at<bf16_t>(saved, sv.h2);
   bf16_t* gu = at<bf16_t>(saved, sv.gu);
@@ -528,7 +566,7 @@ int run_mlp_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x2, const 
   {
     ls::GemmArgs g;
     g.M = (int)m.T;
-    g.N = (int)(2 * ((m.I + 63) / 64) * 64);
+    g.N = (int)glu_cols(m);
     g.K = (int)m.H;
     g.A = h2;
     g.lda = m.H;
@@ -542,6 +580,8 @@ int run_mlp_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x2, const 
     g.ldc = 2 * m.I;
     g.act = act;
     g.glu_I = (int)m.I;
+    g.kpart = kpart;
+    g.kpart_floats = kpart_floats;
     LS_STEP("gate/up projection", st, ls::gemm(g, st));
   }
   if (!down) return LS_OK;
@@ -558,6 +598,8 @@ int run_mlp_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x2, const 
     g.R = x2;
     g.C = y;
     g.ldc = m.H;
+    g.kpart = kpart;
+    g.kpart_floats = kpart_floats;
     LS_STEP("down projection", st, ls::gemm(g, st));
   }
   return LS_OK;
@@ -591,6 +633,8 @@ int run_mlp_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x2, const 
     g.ldc = 2 * m.I;
     g.gu_in = gu;
     g.glu_I = (int)m.I;
+    g.kpart = at<float>(ws, wl.kpart);
+    g.kpart_floats = wl.kpart_floats;
     LS_STEP("dact", st, ls::gemm(g, st));
   }
   // dh2 and dWg/dWu follow dact, which has just written dgu, so they read
@@ -610,6 +654,8 @@ int run_mlp_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x2, const 
     g.epi = ls::EPI_BF16;
     g.C = dh2;
     g.ldc = m.H;
+    g.kpart = at<float>(ws, wl.kpart);
+    g.kpart_floats = wl.kpart_floats;
     LS_STEP("dh2", st, ls::gemm(g, st));
   }
   {  // dWg, dWu (+)= [dg du]^T h2
@@ -686,6 +732,7 @@ int64_t logits_rows(const ls_stack_cfg& c) {
 struct StackWs {
   size_t tg, counts, rows, xs, xmid, hf, rf, logits, dh, dxa, dxb, partial, sets, set_stride, dx2, scratch, total;
   size_t asv, msv, x2;  // offsets inside one set
+  int64_t head_kpart_floats;  // at the start of scratch
 };
 StackWs stack_ws_layout(const ls_stack_cfg& c) {
   const Dims m = dims_of(c.block);
@@ -707,7 +754,12 @@ StackWs stack_ws_layout(const ls_stack_cfg& c) {
   w.dxb = k.take(act);
   w.partial = k.take(norm_partial_bytes(m));
   w.dx2 = k.take(act);
-  w.scratch = k.take(std::max(attn_ws_layout(m).total, mlp_ws_layout(m).total));
+  w.head_kpart_floats = max_kpart_floats({
+      product(ls::EPI_BF16, true, true, logits_rows(c), c.vocab, m.H),   // logits
+      product(ls::EPI_BF16, true, false, logits_rows(c), m.H, c.vocab),  // dh head
+      product(ls::EPI_F32, false, false, c.vocab, m.H, logits_rows(c)),  // dE head
+  });
+  w.scratch = k.take(std::max({attn_ws_layout(m).total, mlp_ws_layout(m).total, (size_t)w.head_kpart_floats * 4}));
   Carver one;
   w.asv = one.take(attn_saved_layout(m).total);
   w.msv = one.take(mlp_saved_layout(m).total);
@@ -797,7 +849,12 @@ int ls_mlp_fwd(const ls_block_cfg* cfg, const ls_bf16* x2, const ls_block_weight
   if (workspace) out.push_back({workspace, workspace_bytes, "workspace"});
   weight_ranges(m, w, false, true, in);
   if (int e = check_ranges(in, out)) return e;
-  return run_mlp_fwd(*cfg, m, (const bf16_t*)x2, w, (bf16_t*)y, mlp_saved, (hipStream_t)stream);
+  // the forward pass runs without scratch too, but splits no product then
+  const MlpWs wl = mlp_ws_layout(m);
+  const bool scratch = workspace && workspace_bytes >= wl.total;
+  return run_mlp_fwd(*cfg, m, (const bf16_t*)x2, w, (bf16_t*)y, mlp_saved,
+                     scratch ? at<float>(workspace, wl.kpart) : nullptr, scratch ? wl.kpart_floats : 0,
+                     (hipStream_t)stream);
 }
 
 int ls_mlp_bwd(const ls_block_cfg* cfg, const ls_bf16* x2, const ls_block_weights* w, const void* mlp_saved,
@@ -841,7 +898,8 @@ int ls_block_fwd_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_w
   void* scratch = at<char>(workspace, bl.scratch);
   const int acc = accumulate != 0;
   if (int e = run_attn_fwd(*cfg, m, (const bf16_t*)x, w, x2, asv, scratch, st)) return e;
-  if (int e = run_mlp_fwd(*cfg, m, x2, w, (bf16_t*)y, msv, st)) return e;
+  const MlpWs ml = mlp_ws_layout(m);
+  if (int e = run_mlp_fwd(*cfg, m, x2, w, (bf16_t*)y, msv, at<float>(scratch, ml.kpart), ml.kpart_floats, st)) return e;
   if (int e = run_mlp_bwd(*cfg, m, x2, w, msv, (const bf16_t*)dy, dx2, g, acc, scratch, st)) return e;
   return run_attn_bwd(*cfg, m, (const bf16_t*)x, w, asv, dx2, (bf16_t*)dx, g, acc, scratch, st);
 }
@@ -1155,6 +1213,7 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
   bf16_t* dxb = at<bf16_t>(workspace, wl.dxb);
   bf16_t* dx2 = at<bf16_t>(workspace, wl.dx2);
   void* scratch = at<char>(workspace, wl.scratch);
+  const MlpWs ml = mlp_ws_layout(m);
 
   // forward: embedding, blocks (keeping every block's input), final norm
   LS_STEP("embedding fwd", st, ls::embed_fwd(m.T, (int)m.H, (int)V, ids, E, xs(0), st));
@@ -1165,7 +1224,9 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
   for (int l = 0; l < L; ++l) {
     char* sv = set(l);
     if (int e = run_attn_fwd(bc, m, xs(l), &w->layers[l], x2_of(l), sv + wl.asv, scratch, st)) return e;
-    if (int e = run_mlp_fwd(bc, m, x2_of(l), &w->layers[l], xs(l + 1), sv + wl.msv, st, !cfg->recompute)) return e;
+    if (int e = run_mlp_fwd(bc, m, x2_of(l), &w->layers[l], xs(l + 1), sv + wl.msv, at<float>(scratch, ml.kpart),
+                            ml.kpart_floats, st, !cfg->recompute))
+      return e;
   }
   LS_STEP("rmsnorm fwd", st,
           ls::rmsnorm_fwd(m.T, (int)m.H, bc.rms_eps, xs(L), (const bf16_t*)w->final_norm, hf, rf, st));
@@ -1187,6 +1248,8 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
       a.epi = ls::EPI_BF16;
       a.C = logits;
       a.ldc = V;
+      a.kpart = (float*)scratch;
+      a.kpart_floats = wl.head_kpart_floats;
       LS_STEP("logits", st, ls::gemm(a, st));
     }
     LS_STEP("cross-entropy", st, ls::ce_rows(tc, (int)V, logits, tg + t0, counts, rows + t0, st));
@@ -1203,6 +1266,8 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
       a.epi = ls::EPI_BF16;
       a.C = dh + t0 * m.H;
       a.ldc = m.H;
+      a.kpart = (float*)scratch;
+      a.kpart_floats = wl.head_kpart_floats;
       LS_STEP("dh head", st, ls::gemm(a, st));
     }
     {  // dE (+)= dz^T h
@@ -1220,6 +1285,8 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
       a.F[0] = g->embed;
       a.ldf = m.H;
       a.accumulate = (t0 > 0) || acc;
+      a.kpart = (float*)scratch;
+      a.kpart_floats = wl.head_kpart_floats;
       LS_STEP("dE head", st, ls::gemm(a, st));
     }
   }
@@ -1237,7 +1304,9 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
     bf16_t* x2 = x2_of(l);
     if (cfg->recompute) {  // the saved state of both sub-layers; x2 and y are known
       if (int e = run_attn_fwd(bc, m, xs(l), &w->layers[l], x2, sv + wl.asv, scratch, st, false)) return e;
-      if (int e = run_mlp_fwd(bc, m, x2, &w->layers[l], nullptr, sv + wl.msv, st, true, false)) return e;
+      if (int e = run_mlp_fwd(bc, m, x2, &w->layers[l], nullptr, sv + wl.msv, at<float>(scratch, ml.kpart),
+                              ml.kpart_floats, st, true, false))
+        return e;
     }
     if (int e = run_mlp_bwd(bc, m, x2, &w->layers[l], sv + wl.msv, dcur, dx2, &g->layers[l], acc, scratch, st))
       return e;

@@ -178,6 +178,16 @@ LS_DEV void sync_lds() {
   asm volatile("" ::: "memory");
 }
 
+// The same, leaving the wave's newest N vector-memory operations in flight.
+template <int N>
+LS_DEV void sync_lds_keep() {
+  static_assert(N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);  // vmcnt(N) lgkmcnt(0)
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 LS_DEV float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));

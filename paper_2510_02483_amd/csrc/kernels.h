@@ -51,19 +51,26 @@ struct GemmArgs {
   int f_start[3] = {0, 1 << 30, 1 << 30};
   int64_t ldf = 0;
   int accumulate = 0;
-  // EPI_F32: fp32 workspace for splitting K over workgroups when the output
-  // tiles fill at most half the compute units ((slices - 1) * M * N floats,
-  // see gemm_kpart_floats); null or smaller means fewer slices or none.
+  // fp32 workspace for splitting K over workgroups when the output tiles alone
+  // would leave compute units idle (slices * M * N floats, one slice fewer for
+  // EPI_F32, see gemm_kpart_floats); null or smaller means fewer slices or none.
   float* kpart = nullptr;
   int64_t kpart_floats = 0;
-  int ksplit = 1;  // slices of K (set by gemm())
+  int ksplit = 1;   // slices of K (set by gemm())
   int group_m = 8;  // tile rows per group of the launch order (set by the launch)
 };
 
 hipError_t gemm(const GemmArgs& a, hipStream_t s);
-// Floats of GemmArgs::kpart with which an EPI_F32 product of this shape runs
-// with its full split of K (0: it is not split).
-int64_t gemm_kpart_floats(int M, int N, int K);
+// Floats of GemmArgs::kpart with which a product of this shape and epilogue
+// runs with its full split of K (0: it is not split).
+int64_t gemm_kpart_floats(const GemmArgs& a);
+// The launches behind gemm(), one per operand layout: a tile shape the epilogue
+// has, with a.ksplit and a.group_m set.  TILE_128_DEEP: four LDS stages, one
+// workgroup per CU; TILE_128: two stages, two workgroups per CU.
+enum GemmTile { TILE_256, TILE_256x192, TILE_192x256, TILE_192, TILE_128, TILE_128_DEEP };
+hipError_t gemm_nt(const GemmArgs& a, GemmTile t, hipStream_t s);
+hipError_t gemm_nn(const GemmArgs& a, GemmTile t, hipStream_t s);
+hipError_t gemm_tn(const GemmArgs& a, GemmTile t, hipStream_t s);
 // Force the tile shape of later gemm launches (bm, bn in {256, 192}; 0, 0 =
 // automatic).  Variants that only exist as 256 x 256 ignore it.  -1 on bad sizes.
 int gemm_tile_override(int bm, int bn);

@@ -32,7 +32,7 @@ import os
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 TRAFFIC_JSON = os.path.join(ROOT, "profiles", "traffic.json")
-KERNEL_SOURCES = ("gemm.hip", "common.h", "kernels.h")
+KERNEL_SOURCES = ("gemm.hip", "gemm_tile.h", "gemm_nt.hip", "gemm_nn.hip", "gemm_tn.hip", "common.h", "kernels.h")
 
 
 def sources_hash() -> str:

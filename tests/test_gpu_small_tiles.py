@@ -1,0 +1,108 @@
+"""Matrix products on few tokens: 128 x 128 tiles with four LDS stages, their
+two-stage form when there are more tiles than compute units, and products whose
+K is split over workgroups, against fp64.
+
+Tolerances: a bf16 result (8 significant bits) differs from fp64 by its own rounding, 2^-8 of its
+value, plus fp32 sums of K <= 600 products (below 600 * 2^-24); an fp32 one by
+the sums alone."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2510_02483_amd import configs, inputs, lib as L
+
+from gpu_util import GRAD_TOL, OUT_TOL, bf16_randn, f64, fro_rel, max_rel, need_gpu, oracle_block, say
+
+pytestmark = pytest.mark.gpu
+
+BF16_TOL = 2.0 ** -8 + 1e-4
+F32_TOL = 600 * 2.0 ** -24
+
+# edges of the 128 x 128 tile; K: 1..9 whole k tiles of 64 (fewer than the four
+# stages, exactly four, one pass of the unrolled loop and every remainder) and ragged ones
+MN = [(8, 8), (120, 136), (128, 128), (136, 264), (264, 120)]
+KS = [8, 64, 72, 128, 192, 256, 264, 320, 384, 448, 512, 520, 576]
+
+
+@pytest.mark.parametrize("K", KS)
+def test_small_products(K):
+    need_gpu()
+    for M, N in MN:
+        say(f"small products M={M} N={N} K={K}")
+        A, B = bf16_randn((M, K), 1), bf16_randn((N, K), 2)
+        ref = f64(A) @ f64(B).T
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        L.ls_gemm_nt(A, B, C)
+        torch.cuda.synchronize()
+        assert max_rel(f64(C), ref) < BF16_TOL
+        C.fill_(float("nan"))
+        L.ls_gemm_nn(A, B.t().contiguous(), C)
+        torch.cuda.synchronize()
+        assert max_rel(f64(C), ref) < BF16_TOL
+        F = torch.full((M, N), 0.25, dtype=torch.float32, device="cuda")
+        L.ls_gemm_tn(A.t().contiguous(), B.t().contiguous(), F, accumulate=True)
+        torch.cuda.synchronize()
+        assert max_rel(f64(F) - 0.25, ref) < F32_TOL
+
+
+# 17 x 21 = 357 tiles of 128 x 128: more than the compute units, fewer than two per unit
+@pytest.mark.parametrize("K", [64, 136, 320])
+def test_more_tiles_than_units(K):
+    need_gpu()
+    M, N = 2056, 2568
+    say(f"two tiles per unit M={M} N={N} K={K}")
+    A, B = bf16_randn((M, K), 3), bf16_randn((N, K), 4)
+    ref = f64(A) @ f64(B).T
+    C = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    L.ls_gemm_nt(A, B, C)
+    torch.cuda.synchronize()
+    assert max_rel(f64(C), ref) < BF16_TOL
+    L.ls_gemm_nn(A, B.t().contiguous(), C)
+    torch.cuda.synchronize()
+    assert max_rel(f64(C), ref) < BF16_TOL
+
+
+# 72 tokens against a width of 4104: every product of the MLP, and those of the
+# attention layer whose K is the width (first case: 128-wide heads) or the heads'
+# features (second: 64-wide), splits its K; ragged in every dimension
+SPLIT_D128 = configs.BlockConfig("split-d128", 31, batch=1, seq=72, hidden=4104, n_q_heads=4, n_kv_heads=2,
+                                 head_dim=128, intermediate=4616, rope_theta=1e4)
+SPLIT_D64 = configs.BlockConfig("split-d64", 32, batch=2, seq=36, hidden=4104, n_q_heads=72, n_kv_heads=8, head_dim=64,
+                                intermediate=264, rope_theta=1e4)
+
+
+@pytest.mark.parametrize("c", [SPLIT_D128, SPLIT_D64], ids=lambda c: c.name)
+def test_split_products(c):
+    need_gpu()
+    say(f"split products {c.name}")
+    host = inputs.make_inputs(c, gamma="random")
+    blk = L.Block(c, host)
+    blk.step()
+    torch.cuda.synchronize()
+    fwd, gr = oracle_block(c, inputs.to_f64(host))
+    shp = (c.batch, c.seq, c.hidden)
+    assert max_rel(f64(blk.y).reshape(shp), fwd["y"]) < OUT_TOL
+    assert fro_rel(f64(blk.dx).reshape(shp), gr["dx"]) < GRAD_TOL
+    for n in L.WEIGHTS:
+        assert fro_rel(f64(blk.grads[n]), gr[n]) < GRAD_TOL, n
+
+
+def test_mlp_forward_with_and_without_scratch():
+    """The MLP forward runs unsplit without a workspace: the same up to the order of its fp32 sums."""
+    need_gpu()
+    c = SPLIT_D128
+    sizes = L.ls_query_sizes(c)
+    unsplit = 2 * c.tokens * (2 * c.intermediate + c.hidden) + 4 * (c.tokens + 31) // 8 * c.hidden
+    assert sizes["mlp_workspace"] > unsplit  # room for partial sums: some product of this shape splits
+    host = inputs.make_inputs(c, gamma="random")
+    w = {n: host[n].cuda() for n in L.WEIGHTS}
+    x = host["x"].cuda().view(c.tokens, c.hidden)
+    out = []
+    for ws in (None, torch.empty(sizes["mlp_workspace"], dtype=torch.uint8, device="cuda")):
+        y = torch.empty_like(x)
+        saved = torch.empty(sizes["mlp_saved"], dtype=torch.uint8, device="cuda")
+        L.ls_mlp_fwd(c, x, w, y, saved, ws)
+        torch.cuda.synchronize()
+        out.append(f64(y))
+    # one bf16 unit in the last place (2^-7) where a sum lies at a rounding boundary
+    assert np.max(np.abs(out[0] - out[1])) <= 2.0 ** -7 * np.max(np.abs(out[0]))
