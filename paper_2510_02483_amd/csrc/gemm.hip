@@ -138,7 +138,8 @@ std::atomic<int> g_tile_override{0};  // 0: automatic, else 1000 * BM + BN
 // takes and the time of one workgroup, k tiles x time per k tile + fixed part
 // (first loads, epilogue, hand-over), with constants measured on the card in us:
 //   256 x 256        1.3 per k tile with the chip full (1.05 with a quarter of it), fixed 9
-//   narrower sides   proportional to the area, 10% more per 192-wide side (more LDS traffic per flop)
+//   narrower sides   proportional to the area, 10% more per 192-wide side (more LDS traffic per flop),
+//                    3% for 192 columns with a k-contiguous A (whose B has a third LDS stage)
 //   128 x 128        one workgroup per CU, four LDS stages: 0.49 per k tile full, 0.34 at a third
 //                    of the chip, fixed 4.5; two per CU with two stages (more tiles than CUs):
 //                    0.97 per k tile of the pair, fixed 6; 12% more with a k-strided operand
@@ -205,7 +206,8 @@ Plan make_plan(const GemmArgs& a, int64_t kpart_floats) {
       us = (double)((wgs + slots - 1) / slots) * (kt * per + (p.deep ? 4.5 : 6.0));
     } else {
       const double fill = std::min(1.0, (double)wgs / ncu);
-      const double per = (0.95 + 0.35 * fill) * (bm * bn / 65536.0) * (bm == 192 ? 1.1 : 1.0) * (bn == 192 ? 1.1 : 1.0);
+      const double per = (0.95 + 0.35 * fill) * (bm * bn / 65536.0) * (bm == 192 ? 1.1 : 1.0) *
+                         (bn == 192 ? (a.a_kcontig ? 1.03 : 1.1) : 1.0);
       us = (double)((wgs + ncu - 1) / ncu) * (kt * per + 9.0);
     }
     if (ks > 1) us += 4.5 + (double)ks * a.M * a.N * 4.0 / 2.5e6;

@@ -69,6 +69,9 @@ constexpr uint32_t OOB = LS_OOB;
 #ifndef GEMM_LOAD_SPAN_NT
 #define GEMM_LOAD_SPAN_NT 45  // the same for the forward (NT) products, whose loop has no transposing reads
 #endif
+#ifndef GEMM_LOAD_SPAN_A
+#define GEMM_LOAD_SPAN_A 30  // with one more B stage: share of the slots over which A's loads are spread
+#endif
 #ifndef GEMM_READ_AHEAD
 #define GEMM_READ_AHEAD 2  // k-steps between a fragment read and its MFMAs
 #endif
@@ -388,7 +391,7 @@ LS_DEV void small_epilogue(const GemmArgs& p, const f32x16 (&acc)[TM][TN], int m
   }
 }
 
-template <bool AK, bool BKC, int EPI, int BM, int BN, int NW, int ST>
+template <bool AK, bool BKC, int EPI, int BM, int BN, int NW, int ST, int SB>
 __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
   // NW waves: 4 (one per SIMD, 2 x 2 wave tiles) or 8 (two per SIMD, 4 x 2)
   static_assert(NW == 4 || NW == 8, "4 or 8 waves");
@@ -414,6 +417,13 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
   static_assert(BAR_AT + NRU <= NMF, "the next tile's first fragments are read within one k-step");
   constexpr int LSPAN = (KSTEPS * NMF * (AK && BKC ? GEMM_LOAD_SPAN_NT : GEMM_LOAD_SPAN_PCT)) / 100;
   static_assert(BAR_AT + LSPAN < KSTEPS * NMF, "every load is issued before the next barrier");
+  // ST LDS stages of A tiles and SB of B tiles, SB = ST or ST + 1.  With one
+  // more B stage a period's loads are A's of tile kt + ST first, then B's of
+  // tile kt + SB, which need not have landed at the next barrier: A's go out
+  // early in the period and B's are spread over all of the rest.
+  static_assert(SB == ST || SB == ST + 1, "at most one more stage of B");
+  constexpr int LSPAN_A = (KSTEPS * NMF * GEMM_LOAD_SPAN_A) / 100;
+  constexpr int LSPAN_B = (KSTEPS * NMF * 95) / 100 - LSPAN_A - BAR_AT;
   // Fragments are read RA k-steps ahead of the MFMAs that use them (RA + 1
   // register buffers; with RA = 2 four, one per k-step of a tile), so that a
   // read delayed by the buffer->LDS writes does not hold up the matrix core.
@@ -426,11 +436,11 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
   constexpr bool GLU = EPI == EPI_GLU_FWD;
   constexpr uint32_t A_BYTES = AK ? (BM / 8) * KC_PITCH : BM * KT * 2;
   constexpr uint32_t B_BYTES = BKC ? (BN / 8) * KC_PITCH : BN * KT * 2;
-  constexpr uint32_t STAGE_BYTES = A_BYTES + B_BYTES;
+  constexpr uint32_t RING_BYTES = ST * A_BYTES + SB * B_BYTES;  // [A stages | B stages]
   // the epilogue stages results in the first 128 KB
-  constexpr uint32_t LDS_BYTES = SMALL || ST * STAGE_BYTES > 4 * TILE_ELEMS * 2 ? ST * STAGE_BYTES : 4 * TILE_ELEMS * 2;
-  // Two LDS stages of [A tile | B tile].  The buffer->LDS loads are inline
-  // assembly the compiler does not see, so the stage can be picked at run time.
+  constexpr uint32_t LDS_BYTES = SMALL || RING_BYTES > 4 * TILE_ELEMS * 2 ? RING_BYTES : 4 * TILE_ELEMS * 2;
+  // The buffer->LDS loads are inline assembly the compiler does not see, so the
+  // stage can be picked at run time.
   constexpr uint32_t PF_LDS = EPI == EPI_GLU_BWD ? 1024 : 0;
   __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES + PF_LDS];
 
@@ -493,15 +503,19 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
     if constexpr (!KSEG) lb.r = rsrc(p.B[0], clamp_bytes((int64_t)K * p.ldb * 2));
   }
 
-  // The load cursor: first k of the next tile to load, its valid k count and
-  // the scalar offsets of both operands (B's resource follows its segment).
-  int ck = 0, kval = 0;
+  // The load cursors: first k of the next A and B tile to load, its valid k
+  // count and scalar offset (B's resource follows its segment).
+  int cka = 0, kva = 0, ckb = 0, kvb = 0;
   uint32_t soa = 0, sob = 0;
-  auto set_cursor = [&](int k0) {
-    ck = k0;
-    const int se = seg_end(k0);
-    kval = min(KT, se - k0);
+  auto cursor_a = [&](int k0) {
+    cka = k0;
+    kva = min(KT, seg_end(k0) - k0);
     soa = AK ? (uint32_t)(k0 * 2) : (uint32_t)((int64_t)k0 * p.lda * 2);
+  };
+  auto cursor_b = [&](int k0) {
+    ckb = k0;
+    const int se = seg_end(k0);
+    kvb = min(KT, se - k0);
     if constexpr (KSEG) {
       const int sg = k0 >= S2 ? 2 : (k0 >= S1 ? 1 : 0);
       const int st = sg == 2 ? S2 : (sg == 1 ? S1 : 0);
@@ -512,16 +526,21 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
       sob = BKC ? (uint32_t)(k0 * 2) : (uint32_t)((int64_t)k0 * p.ldb * 2);
     }
   };
-  // The next tile's cursor.
-  auto advance = [&]() { set_cursor(ck + kval); };
   const uint32_t lds0 = lds_offset(&lds[0]);
-  const uint32_t ma = lds0 + wave * NA * (AK ? KC_PITCH : 1024), mb = lds0 + A_BYTES + wave * NB * (BKC ? KC_PITCH : 1024);
-  // Load q of the tile at the cursor (A loads first) into the stage at byte
-  // offset stage_off; full_c: std::true_type where that tile is known to be whole.
-  auto issue = [&](auto full_c, int q, uint32_t stage_off) {
+  const uint32_t ma = lds0 + wave * NA * (AK ? KC_PITCH : 1024);
+  const uint32_t mb = lds0 + ST * A_BYTES + wave * NB * (BKC ? KC_PITCH : 1024);
+  // Load q of a period (A loads first) into stage `st` of its operand; the
+  // last load of an operand moves its cursor.  full_c: std::true_type where the
+  // tile is known to be whole.
+  auto issue = [&](auto full_c, int q, int st) {
     constexpr bool FULL = decltype(full_c)::value;
-    if (q < NA) load_one<AK, NA, BM, FULL>(la, q, soa, kval, ma + stage_off, wave);
-    else load_one<BKC, NB, BN, FULL>(lb, q - NA, sob, kval, mb + stage_off, wave);
+    if (q < NA) {
+      load_one<AK, NA, BM, FULL>(la, q, soa, kva, ma + (uint32_t)st * A_BYTES, wave);
+      if (q == NA - 1) cursor_a(cka + kva);
+    } else {
+      load_one<BKC, NB, BN, FULL>(lb, q - NA, sob, kvb, mb + (uint32_t)st * B_BYTES, wave);
+      if (q == NL - 1) cursor_b(ckb + kvb);
+    }
   };
 
   f32x16 acc[TM][TN];
@@ -540,9 +559,9 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
   auto bcol = [&](int j) { return SPLITC ? 64 * j + 32 * wn : wn * WN + 32 * j; };
   u32x4 af[NBUF][TM], bfr[NBUF][TN];
   // Fragment u of a k-step: A fragments 0 .. TM-1, then B fragments.
-  auto read_unit = [&](int stage, int s, int buf, int u) {
-    const char* as = lds + stage * STAGE_BYTES;
-    const char* bs = as + A_BYTES;
+  auto read_unit = [&](int sta, int stb, int s, int buf, int u) {
+    const char* as = lds + sta * A_BYTES;
+    const char* bs = lds + ST * A_BYTES + stb * B_BYTES;
     if (u < TM) {
       af[buf][u] = AK ? frag_kc(as, wm * WM + 32 * u + lr, s, lh) : frag_ks<BM>((const bf16_t*)as, wm * WM + 32 * u, s, lane);
     } else {
@@ -553,7 +572,10 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
 
   // MFMA slot (counted from the start of the barrier's k-step) of load q of
   // the tile after next.
-  constexpr auto slot_of = [](int q) { return BAR_AT + (q * LSPAN) / NL; };
+  constexpr auto slot_of = [](int q) {
+    if (SB == ST) return BAR_AT + (q * LSPAN) / NL;
+    return q < NA ? BAR_AT + (q * LSPAN_A) / NA : BAR_AT + LSPAN_A + ((q - NA) * LSPAN_B) / NB;
+  };
   constexpr auto bufi = [](int s) { return NBUF == 4 ? s : s & 1; };
 
   // One 64-k tile in stage `cur` (NX: how many of the next two tiles exist).
@@ -583,17 +605,15 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
     pf_voff = (uint32_t)(((int64_t)(lane >> 3) * ld2 + arr * p.glu_I + n0 + seg * 64) * 2);
   }
   const int pf_first = nk - 36;
-  // cur_c: the stage, a compile-time constant in the unrolled loop over whole
-  // tiles (every LDS address is then a register plus an immediate) or an int;
-  // full_c: every tile this one loads is whole (no lane masking).
-  // PH says which later tiles exist: 3 = kt + ST and all before it, 2 = kt + ST - 1,
-  // 1 = kt + 1, 0 = none.
-  auto tile = [&](auto ph_c, auto cur_c, auto full_c) {
+  // ca_c, cb_c: the stages, compile-time constants in the unrolled loop over
+  // whole tiles (every LDS address is then a register plus an immediate) or
+  // ints; full_c: every tile this one loads is whole (no lane masking).
+  // PH: tiles after this one, at most SB.
+  auto tile = [&](auto ph_c, auto ca_c, auto cb_c, auto full_c) {
     constexpr int PH = decltype(ph_c)::value;
-    const int cur = cur_c;
-    const int nxt = ST == 2 ? cur ^ 1 : (cur + 1) % ST;
-    const uint32_t here = (uint32_t)cur * STAGE_BYTES;
-    const uint32_t late = (uint32_t)(ST == 2 ? cur ^ 1 : (cur + ST - 1) % ST) * STAGE_BYTES;
+    const int ca = ca_c, cb = cb_c;
+    const int na = ST == 2 ? ca ^ 1 : (ca + 1) % ST, nb = SB == 2 ? cb ^ 1 : (cb + 1) % SB;          // next tile's
+    const int pa = ST == 2 ? ca ^ 1 : (ca + ST - 1) % ST, pb = SB == 2 ? cb ^ 1 : (cb + SB - 1) % SB;  // previous tile's
     static_for<KSTEPS>([&](auto s_c) {
       constexpr int s = s_c;
       constexpr int buf = bufi(s);
@@ -601,7 +621,8 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
       static_for<NMF>([&](auto i_c) {
         constexpr int i = i_c;
         if constexpr (PH >= 1 && s == BS && i == BAR_AT) {
-          if constexpr (ST > 2 && PH >= 2) sync_lds_keep<(ST - 2) * NL>();
+          constexpr int KEEP = (ST - 2) * NL + (SB > ST ? NB : 0);  // loads newer than the next tile's
+          if constexpr (KEEP > 0 && PH >= SB - 1) sync_lds_keep<KEEP>();
           else sync_lds();
           if constexpr (EPI == EPI_GLU_BWD && !SMALL) {
             const int j = kt - pf_first;
@@ -612,85 +633,77 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
         __builtin_amdgcn_sched_barrier(0);
         acc[i / TN][i % TN] = mfma32(bfr[buf][i % TN], af[buf][i / TN], acc[i / TN][i % TN]);
         if constexpr (t < KSTEPS) {
-          if constexpr (i < NRU) read_unit(cur, t, bufi(t), i);
+          if constexpr (i < NRU) read_unit(ca, cb, t, bufi(t), i);
         } else if constexpr (PH >= 1) {
           constexpr int u = s == BS ? i - BAR_AT : i;
-          if constexpr (u >= 0 && u < NRU) read_unit(nxt, t - KSTEPS, bufi(t - KSTEPS), u);
+          if constexpr (u >= 0 && u < NRU) read_unit(na, nb, t - KSTEPS, bufi(t - KSTEPS), u);
         }
         static_for<NL>([&](auto q_c) {
           constexpr int q = q_c;
           constexpr int at = slot_of(q) + BS * NMF;  // tile-relative slot of load q (may be in the next tile)
-          // the later loads of tile kt + ST - 1 (its first ones went out in the previous tile)
-          if constexpr (PH >= 2 && at >= KSTEPS * NMF && at - KSTEPS * NMF == s * NMF + i) {
-            issue(full_c, q, late);
-            if constexpr (q == NL - 1) advance();
-          }
-          // the first loads of tile kt + ST, into this stage
-          if constexpr (PH >= 3 && at < KSTEPS * NMF && at == s * NMF + i) {
-            issue(full_c, q, here);
-            if constexpr (q == NL - 1) advance();
-          }
+          constexpr int S = q < NA ? ST : SB;
+          // the later loads of the previous tile's period (tile kt + S - 1)
+          if constexpr (PH >= S - 1 && at >= KSTEPS * NMF && at - KSTEPS * NMF == s * NMF + i)
+            issue(full_c, q, q < NA ? pa : pb);
+          // the first loads of this tile's period (tile kt + S), into this tile's stage
+          if constexpr (PH >= S && at < KSTEPS * NMF && at == s * NMF + i) issue(full_c, q, q < NA ? ca : cb);
         });
         __builtin_amdgcn_sched_barrier(0);
       });
     });
   };
 
-  // Prologue: tiles 0 .. ST-2 whole, then the loads of tile ST-1 that the
-  // tile before tile 0 would have issued in its last k-steps; wait for tile 0.
-  constexpr int FIRST = [] {
+  // Prologue: A tiles 0 .. ST-2 and B tiles 0 .. SB-2 whole, then the loads
+  // that the tile before tile 0 would have issued in its last k-steps; wait for
+  // tile 0.
+  constexpr int FIRST = [slot_of] {
     int n = 0;
-    for (int q = 0; q < NL; ++q) n += BAR_AT + (q * LSPAN) / NL + BS * NMF < KSTEPS * NMF;
+    for (int q = 0; q < NL; ++q) n += slot_of(q) + BS * NMF < KSTEPS * NMF;
     return n;
   }();
-  set_cursor(kbeg);
+  cursor_a(kbeg);
+  cursor_b(kbeg);
 #pragma unroll
-  for (int t = 0; t < ST - 1; ++t) {
+  for (int t = 0; t < SB - 1; ++t) {
     if (t > 0 && t >= nk) break;
 #pragma unroll
-    for (int q = 0; q < NL; ++q) issue(std::false_type{}, q, t * STAGE_BYTES);
-    advance();
+    for (int q = t < ST - 1 ? 0 : NA; q < NL; ++q) issue(std::false_type{}, q, t);
   }
-  if (nk > ST - 1) {
 #pragma unroll
-    for (int q = 0; q < FIRST; ++q) issue(std::false_type{}, q, (ST - 1) * STAGE_BYTES);
-    if (FIRST == NL) advance();
-    LS_WAIT_VMCNT((ST - 2) * NL + FIRST);
-  } else {
-    LS_WAIT_VMCNT(0);
-  }
+  for (int q = 0; q < FIRST; ++q)
+    if (nk > (q < NA ? ST : SB) - 1) issue(std::false_type{}, q, (q < NA ? ST : SB) - 1);
+  if (nk > SB - 1) LS_WAIT_VMCNT((ST - 2) * NA + (SB - 2) * NB + FIRST);
+  else LS_WAIT_VMCNT(0);
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 #pragma unroll
   for (int t = 0; t < RA; ++t)
 #pragma unroll
-    for (int u = 0; u < NRU; ++u) read_unit(0, t, bufi(t), u);
-  using P0 = std::integral_constant<int, 0>;
-  using P1 = std::integral_constant<int, 1>;
-  using P2 = std::integral_constant<int, 2>;
-  using P3 = std::integral_constant<int, 3>;
+    for (int u = 0; u < NRU; ++u) read_unit(0, 0, t, bufi(t), u);
   // Every tile of every k segment whole (k lengths multiples of the tile
-  // depth): no load masks, and with one wave per SIMD ST tiles per pass, one
-  // per stage, so every fragment address is a register plus an immediate (with
-  // two waves per SIMD that copy of the loop needs more registers than a wave
-  // has and spills).
+  // depth): no load masks, and with one wave per SIMD enough tiles per pass
+  // that every stage is a constant (with two waves per SIMD that copy of the
+  // loop needs more registers than a wave has and spills).
   const bool whole = S1 % KT == 0 && (S2 - S1) % KT == 0 && (K - S2) % KT == 0;
+  using PSB = std::integral_constant<int, SB>;
+  constexpr int PASS = SB == ST ? ST : ST * SB;
   if (whole) {
     if constexpr (NW == 4) {
-      for (; kt + 2 * ST - 1 < nk; kt += ST)
-        static_for<ST>([&](auto c) { tile(P3{}, c, std::true_type{}); });
-    } else {
-      for (; kt + ST < nk; ++kt) tile(P3{}, kt % ST, std::true_type{});
+      for (; kt + PASS + SB - 1 < nk; kt += PASS)
+        static_for<PASS>([&](auto c) {
+          tile(PSB{}, std::integral_constant<int, c % ST>{}, std::integral_constant<int, c % SB>{}, std::true_type{});
+        });
     }
+    for (; kt + SB < nk; ++kt) tile(PSB{}, kt % ST, kt % SB, std::true_type{});
   }
-  for (; kt + ST < nk; ++kt) tile(P3{}, kt % ST, std::false_type{});
-  if (kt + ST - 1 < nk) {
-    tile(P2{}, kt % ST, std::false_type{});
-    ++kt;
-  }
-  if constexpr (ST > 2)
-    for (; kt + 1 < nk; ++kt) tile(P1{}, kt % ST, std::false_type{});
-  tile(P0{}, kt % ST, std::false_type{});
+  for (; kt + SB < nk; ++kt) tile(PSB{}, kt % ST, kt % SB, std::false_type{});
+  static_for<SB>([&](auto c) {  // the last tiles: SB - 1, .., 1, 0 after them
+    constexpr int r = SB - 1 - c;
+    if (kt + r < nk) {
+      tile(std::integral_constant<int, r>{}, kt % ST, kt % SB, std::false_type{});
+      ++kt;
+    }
+  });
   if constexpr (SMALL && EPI != EPI_F32) {
     small_epilogue<EPI, TM, TN>(p, acc, m0 + wm * WM, n0, bcol(0), bcol(1), slice, ks, lr, lh);
     return;
@@ -992,10 +1005,21 @@ constexpr int waves_of() {
   return BM == 256 && (!AK || (!BKC && EPI == EPI_GLU_BWD)) ? 8 : 4;
 }
 
-template <bool AK, bool BKC, int EPI, int BM, int BN, int NW = waves_of<AK, BKC, EPI, BM>(), int ST = 2>
+// Stages of B: three beside two of A for the 256 x 192 tiles of the products
+// with a k-contiguous A (138 KB of LDS).  With two, the loads of a tile had to
+// go out in the first half of a period and were still waited for: 8192 x 3072 x
+// 16384 NN 690 -> 633 us, 8192 x 3072 x 8192 NT 292 -> 286 us.  256 x 256 tiles
+// have no LDS for it, and the weight-gradient (TN) products are no faster
+// (326 -> 330 us for 3072 x 8192 x 8192).
+template <bool AK, int BM, int BN>
+constexpr int b_stages(int st) {
+  return AK && BM == 256 && BN == 192 ? st + 1 : st;
+}
+template <bool AK, bool BKC, int EPI, int BM, int BN, int NW = waves_of<AK, BKC, EPI, BM>(), int ST = 2,
+          int SB = b_stages<AK, BM, BN>(ST)>
 hipError_t launch(const GemmArgs& a, hipStream_t s) {
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_kernel<AK, BKC, EPI, BM, BN, NW, ST>), dim3(tiles * a.ksplit), dim3(NW * 64), 0, s, a);
+  hipLaunchKernelGGL((gemm_kernel<AK, BKC, EPI, BM, BN, NW, ST, SB>), dim3(tiles * a.ksplit), dim3(NW * 64), 0, s, a);
   return hipGetLastError();
 }
 // 128 x 128 tiles with ST LDS stages.
