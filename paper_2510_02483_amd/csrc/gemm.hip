@@ -198,7 +198,10 @@ Plan make_plan(const GemmArgs& a, int64_t kpart_floats) {
     p.bn = bn;
     p.ks = ks;
     double us;
-    if (bm == 128) {
+    if (bn == 128 && bm == 256) {
+      const double fill = std::min(1.0, (double)wgs / ncu);
+      us = (double)((wgs + ncu - 1) / ncu) * (kt * (0.45 + 0.40 * fill) * (nt ? 1.0 : 1.08) + 6.0);
+    } else if (bm == 128) {
       p.deep = wgs <= ncu;
       const int64_t slots = p.deep ? ncu : 2 * ncu;
       const double fill = std::min(1.0, (double)wgs / slots);
@@ -223,8 +226,12 @@ Plan make_plan(const GemmArgs& a, int64_t kpart_floats) {
     const int ks = ksplit_of(a.M, a.N, a.K);
     if (ks > 1) consider(256, 256, ks);
   }
-  // slices at least 8 k tiles deep; 4 columns per access of the partial sums
-  for (int ks = 1; ks <= 8 && (ks == 1 || (ktiles >= 8 * ks && a.N % 4 == 0)); ++ks) consider(128, 128, ks);
+  // slices at least 8 k tiles deep
+  for (int ks = 1; ks <= 8 && (ks == 1 || ktiles >= 8 * ks); ++ks) {
+    consider(128, 128, ks);
+    consider(256, 128, ks);
+    if (ks > 1 && !f32 && a.epi != EPI_GLU_FWD) consider(256, 256, ks);
+  }
   return best;
 }
 
@@ -258,9 +265,13 @@ hipError_t gemm(const GemmArgs& args, hipStream_t s) {
   a.ksplit = p.ks;
   a.group_m = group_rows(a.M, a.N, a.K, p.bm, p.bn);
   const GemmTile t = p.bm == 128 ? (p.deep ? TILE_128_DEEP : TILE_128)
+                     : p.bn == 128 ? TILE_256x128
                                  : p.bm == 256 ? (p.bn == 256 ? TILE_256 : TILE_256x192)
                                                : (p.bn == 256 ? TILE_192x256 : TILE_192);
+  const int epi = a.epi;
+  if (p.ks > 1 && t == TILE_256 && epi != EPI_F32) a.epi = EPI_PART;
   hipError_t e = a.a_kcontig ? (a.b_kcontig ? gemm_nt(a, t, s) : gemm_nn(a, t, s)) : gemm_tn(a, t, s);
+  a.epi = epi;
   if (e != hipSuccess || p.ks == 1) return e;
   const int64_t items = a.epi == EPI_F32 ? (int64_t)a.M * a.N / 4 : (int64_t)a.M * a.N / 8;
   const dim3 grid((unsigned)std::min<int64_t>((items + 255) / 256, 256 * 8)), block(256);

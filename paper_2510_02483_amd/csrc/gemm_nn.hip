@@ -9,17 +9,14 @@ hipError_t gemm_nn(const GemmArgs& a, GemmTile t, hipStream_t s) {
       switch (t) {
         case TILE_256: return launch<true, false, EPI_BF16, 256, 256>(a, s);
         case TILE_256x192: return launch<true, false, EPI_BF16, 256, 192>(a, s);
-        case TILE_128: return launch_small<true, false, EPI_BF16, 2>(a, s);
-        case TILE_128_DEEP: return launch_small<true, false, EPI_BF16, 4>(a, s);
-        default: return hipErrorInvalidValue;
+        default: return launch_narrow<true, false, EPI_BF16>(a, t, s);
       }
     case EPI_GLU_BWD:
       switch (t) {
         case TILE_256: return launch<true, false, EPI_GLU_BWD, 256, 256>(a, s);
-        case TILE_128: return launch_small<true, false, EPI_GLU_BWD, 2>(a, s);
-        case TILE_128_DEEP: return launch_small<true, false, EPI_GLU_BWD, 4>(a, s);
-        default: return hipErrorInvalidValue;
+        default: return launch_narrow<true, false, EPI_GLU_BWD>(a, t, s);
       }
+    case EPI_PART: return t == TILE_256 ? launch<true, false, EPI_PART, 256, 256>(a, s) : hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
 }

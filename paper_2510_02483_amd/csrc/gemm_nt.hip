@@ -9,40 +9,31 @@ hipError_t gemm_nt(const GemmArgs& a, GemmTile t, hipStream_t s) {
       switch (t) {
         case TILE_256: return launch<true, true, EPI_BF16, 256, 256>(a, s);
         case TILE_256x192: return launch<true, true, EPI_BF16, 256, 192>(a, s);
-        case TILE_128: return launch_small<true, true, EPI_BF16, 2>(a, s);
-        case TILE_128_DEEP: return launch_small<true, true, EPI_BF16, 4>(a, s);
-        default: return hipErrorInvalidValue;
+        default: return launch_narrow<true, true, EPI_BF16>(a, t, s);
       }
     case EPI_RESID:
       switch (t) {
         case TILE_256: return launch<true, true, EPI_RESID, 256, 256>(a, s);
         case TILE_256x192: return launch<true, true, EPI_RESID, 256, 192>(a, s);
-        case TILE_128: return launch_small<true, true, EPI_RESID, 2>(a, s);
-        case TILE_128_DEEP: return launch_small<true, true, EPI_RESID, 4>(a, s);
-        default: return hipErrorInvalidValue;
+        default: return launch_narrow<true, true, EPI_RESID>(a, t, s);
       }
     case EPI_ROPE:
       if (a.head_dim == 64) {
         switch (t) {
           case TILE_256: return launch<true, true, EPI_ROPE64, 256, 256>(a, s);
-          case TILE_128: return launch_small<true, true, EPI_ROPE64, 2>(a, s);
-          case TILE_128_DEEP: return launch_small<true, true, EPI_ROPE64, 4>(a, s);
-          default: return hipErrorInvalidValue;
+          default: return launch_narrow<true, true, EPI_ROPE64>(a, t, s);
         }
       }
       switch (t) {
         case TILE_256: return launch<true, true, EPI_ROPE, 256, 256>(a, s);
-        case TILE_128: return launch_small<true, true, EPI_ROPE, 2>(a, s);
-        case TILE_128_DEEP: return launch_small<true, true, EPI_ROPE, 4>(a, s);
-        default: return hipErrorInvalidValue;
+        default: return launch_narrow<true, true, EPI_ROPE>(a, t, s);
       }
     case EPI_GLU_FWD:
       switch (t) {
         case TILE_256: return launch<true, true, EPI_GLU_FWD, 256, 256>(a, s);
-        case TILE_128: return launch_small<true, true, EPI_GLU_FWD, 2>(a, s);
-        case TILE_128_DEEP: return launch_small<true, true, EPI_GLU_FWD, 4>(a, s);
-        default: return hipErrorInvalidValue;
+        default: return launch_narrow<true, true, EPI_GLU_FWD>(a, t, s);
       }
+    case EPI_PART: return t == TILE_256 ? launch<true, true, EPI_PART, 256, 256>(a, s) : hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
 }

@@ -344,7 +344,7 @@ LS_DEV void store_glu_bwd8(const GemmArgs& p, int m, int n, const float da[8]) {
   *(u32x4*)(dst + p.glu_I) = pack8f(du);
 }
 
-// Epilogue of a 128 x 128 tile (all but the fp32 weight gradients): 8 columns
+// Epilogue of a 128-column tile (all but the fp32 weight gradients): 8 columns
 // per lane and step, straight from the registers.  c0, c1: tile-local first
 // columns of the wave's two 32-column blocks.  When K is split, every slice
 // stores its fp32 partial sums ([slice][M][N]) for ksplit_finish_kernel.
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
   constexpr int WM = BM / (NW / 2), WN = BN / 2;  // wave tile
   static_assert(WM % 32 == 0 && WN % 32 == 0, "wave tiles of whole 32 x 32 blocks");
   constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr bool SMALL = BM == 128;  // 128 x 128 tile: ST stages, epilogue straight from the registers
+  constexpr bool SMALL = BN == 128;  // more LDS stages; epilogue straight from the registers
   constexpr int NA = AK ? BM / (8 * NW) : ks_blocks<BM>() / NW;  // loads per wave and tile
   constexpr int NB = BKC ? BN / (8 * NW) : ks_blocks<BN>() / NW;
   constexpr int NL = NA + NB;                                    // loads per wave and tile
@@ -448,8 +448,8 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / 2, wn = wave % 2;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  // fp32 weight gradients may split K: workgroup x runs slice x / tiles of tile x % tiles
-  const int ks = EPI == EPI_F32 || SMALL ? p.ksplit : 1;
+  // K may be split: workgroup x runs slice x / tiles of tile x % tiles
+  const int ks = p.ksplit;
   const int slice = ks > 1 ? (int)blockIdx.x / (tiles_m * tiles_n) : 0;
   int tm, tn;
   map_tile((int)blockIdx.x - slice * tiles_m * tiles_n, tiles_m, tiles_n, p.group_m, tm, tn);
@@ -680,21 +680,24 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
   for (int t = 0; t < RA; ++t)
 #pragma unroll
     for (int u = 0; u < NRU; ++u) read_unit(0, 0, t, bufi(t), u);
-  // Every tile of every k segment whole (k lengths multiples of the tile
-  // depth): no load masks, and with one wave per SIMD enough tiles per pass
-  // that every stage is a constant (with two waves per SIMD that copy of the
-  // loop needs more registers than a wave has and spills).
+  // The leading tiles that are whole (all of them when every k segment is a
+  // multiple of the tile depth, else those of the first segment): no load masks,
+  // and with one wave per SIMD enough tiles per pass that every stage is a
+  // constant, so every fragment address is a register plus an immediate (with
+  // two waves per SIMD that copy of the loop needs more registers than a wave
+  // has and spills).
   const bool whole = S1 % KT == 0 && (S2 - S1) % KT == 0 && (K - S2) % KT == 0;
+  const int nfull = whole ? nk : max(0, min(kend, S1) - kbeg) / KT;
   using PSB = std::integral_constant<int, SB>;
   constexpr int PASS = SB == ST ? ST : ST * SB;
-  if (whole) {
+  {
     if constexpr (NW == 4) {
-      for (; kt + PASS + SB - 1 < nk; kt += PASS)
+      for (; kt + PASS + SB - 1 < nfull; kt += PASS)
         static_for<PASS>([&](auto c) {
           tile(PSB{}, std::integral_constant<int, c % ST>{}, std::integral_constant<int, c % SB>{}, std::true_type{});
         });
     }
-    for (; kt + SB < nk; ++kt) tile(PSB{}, kt % ST, kt % SB, std::true_type{});
+    for (; kt + SB < nfull; ++kt) tile(PSB{}, kt % ST, kt % SB, std::true_type{});
   }
   for (; kt + SB < nk; ++kt) tile(PSB{}, kt % ST, kt % SB, std::false_type{});
   static_for<SB>([&](auto c) {  // the last tiles: SB - 1, .., 1, 0 after them
@@ -706,6 +709,22 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
   });
   if constexpr (SMALL && EPI != EPI_F32) {
     small_epilogue<EPI, TM, TN>(p, acc, m0 + wm * WM, n0, bcol(0), bcol(1), slice, ks, lr, lh);
+    return;
+  }
+  if constexpr (EPI == EPI_PART) {  // a slice's fp32 partial sums ([slice][M][N]) for ksplit_finish_kernel
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int m = m0 + wm * WM + 32 * i + lr;
+      float* row = p.kpart + ((int64_t)slice * p.M + m) * p.N;
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int n = n0 + wn * WN + 32 * j + 8 * q + 4 * lh;
+          if (m < p.M && n < p.N)
+            *(f32x4*)(row + n) = f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        }
+    }
     return;
   }
   sync_lds();  // every wave is done with both stages before they become staging space
@@ -738,7 +757,7 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
     }
   };
 
-  if constexpr (SMALL && EPI != EPI_F32) {
+  if constexpr ((SMALL && EPI != EPI_F32) || EPI == EPI_PART) {
   } else if constexpr (EPI == EPI_F32) {
     // fp32 weight gradients straight from the registers: a lane's 4 columns are
     // 16 contiguous bytes (read-modify-write with accumulate).  Slices 1.. of a
@@ -1000,9 +1019,9 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
 // forward (NT) products and the plain input-gradient ones (whose main loop,
 // with the registers of one wave per SIMD, runs two tiles per pass).  BM = 192
 // tiles keep 4 (a wave tile of 48 rows is not whole 32-row blocks).
-template <bool AK, bool BKC, int EPI, int BM>
+template <bool AK, bool BKC, int EPI, int BM, int BN>
 constexpr int waves_of() {
-  return BM == 256 && (!AK || (!BKC && EPI == EPI_GLU_BWD)) ? 8 : 4;
+  return BM == 256 && BN != 128 && (!AK || (!BKC && EPI == EPI_GLU_BWD)) ? 8 : 4;
 }
 
 // Stages of B: three beside two of A for the 256 x 192 tiles of the products
@@ -1015,17 +1034,22 @@ template <bool AK, int BM, int BN>
 constexpr int b_stages(int st) {
   return AK && BM == 256 && BN == 192 ? st + 1 : st;
 }
-template <bool AK, bool BKC, int EPI, int BM, int BN, int NW = waves_of<AK, BKC, EPI, BM>(), int ST = 2,
+template <bool AK, bool BKC, int EPI, int BM, int BN, int NW = waves_of<AK, BKC, EPI, BM, BN>(), int ST = 2,
           int SB = b_stages<AK, BM, BN>(ST)>
 hipError_t launch(const GemmArgs& a, hipStream_t s) {
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
   hipLaunchKernelGGL((gemm_kernel<AK, BKC, EPI, BM, BN, NW, ST, SB>), dim3(tiles * a.ksplit), dim3(NW * 64), 0, s, a);
   return hipGetLastError();
 }
-// 128 x 128 tiles with ST LDS stages.
-template <bool AK, bool BKC, int EPI, int ST>
-hipError_t launch_small(const GemmArgs& a, hipStream_t s) {
-  return launch<AK, BKC, EPI, 128, 128, 4, ST>(a, s);
+// The 128-column tiles.
+template <bool AK, bool BKC, int EPI>
+hipError_t launch_narrow(const GemmArgs& a, GemmTile t, hipStream_t s) {
+  switch (t) {
+    case TILE_256x128: return launch<AK, BKC, EPI, 256, 128, 4, 3>(a, s);
+    case TILE_128: return launch<AK, BKC, EPI, 128, 128, 4, 2>(a, s);
+    case TILE_128_DEEP: return launch<AK, BKC, EPI, 128, 128, 4, 4>(a, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace

@@ -11,9 +11,7 @@ hipError_t gemm_tn(const GemmArgs& a, GemmTile t, hipStream_t s) {
         case TILE_256x192: return launch<false, false, EPI_F32, 256, 192>(a, s);
         case TILE_192x256: return launch<false, false, EPI_F32, 192, 256>(a, s);
         case TILE_192: return launch<false, false, EPI_F32, 192, 192>(a, s);
-        case TILE_128: return launch_small<false, false, EPI_F32, 2>(a, s);
-        case TILE_128_DEEP: return launch_small<false, false, EPI_F32, 4>(a, s);
-        default: return hipErrorInvalidValue;
+        default: return launch_narrow<false, false, EPI_F32>(a, t, s);
       }
     default: return hipErrorInvalidValue;
   }

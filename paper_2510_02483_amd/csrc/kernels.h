@@ -25,6 +25,7 @@ enum Epilogue {
   EPI_GLU_FWD = 3,  // gu[m][i] = g, gu[m][I+i] = u (C; skipped when null), act[m][i] = silu(g) u
   EPI_GLU_BWD = 4,  // C = dgu: dgu[m][i] = acc u silu'(g), dgu[m][I+i] = acc silu(g)
   EPI_F32 = 5,      // F (fp32, rows split over up to three buffers) (+)= acc
+  EPI_PART = 6,     // kpart[slice] = acc: a slice of a split K (256 x 256 tiles; set by gemm())
 };
 
 struct GemmArgs {
@@ -65,9 +66,10 @@ hipError_t gemm(const GemmArgs& a, hipStream_t s);
 // runs with its full split of K (0: it is not split).
 int64_t gemm_kpart_floats(const GemmArgs& a);
 // The launches behind gemm(), one per operand layout: a tile shape the epilogue
-// has, with a.ksplit and a.group_m set.  TILE_128_DEEP: four LDS stages, one
-// workgroup per CU; TILE_128: two stages, two workgroups per CU.
-enum GemmTile { TILE_256, TILE_256x192, TILE_192x256, TILE_192, TILE_128, TILE_128_DEEP };
+// has, with a.ksplit and a.group_m set.  TILE_256x128: three LDS stages;
+// TILE_128_DEEP: four, one workgroup per CU; TILE_128: two stages, two
+// workgroups per CU.
+enum GemmTile { TILE_256, TILE_256x192, TILE_192x256, TILE_192, TILE_256x128, TILE_128, TILE_128_DEEP };
 hipError_t gemm_nt(const GemmArgs& a, GemmTile t, hipStream_t s);
 hipError_t gemm_nn(const GemmArgs& a, GemmTile t, hipStream_t s);
 hipError_t gemm_tn(const GemmArgs& a, GemmTile t, hipStream_t s);
