@@ -12,7 +12,7 @@ namespace {
 
 constexpr int NORM_WAVES = 4;           // forward: waves per workgroup, one row per wave
 constexpr int BWD_WAVES = 8;            // backward: waves per workgroup, two rows per wave at a time
-constexpr int BWD_ROWS_PER_BLOCK = 32;  // rows whose gain gradient one workgroup sums
+constexpr int BWD_MAX_ROWS = 32;        // most rows whose gain gradient one workgroup sums
 constexpr int SUM_GROUPS = 8;           // column sum: part groups per workgroup
 
 LS_DEV void unpack8(const u32x4 w, float f[8]) {
@@ -67,10 +67,10 @@ __global__ __launch_bounds__(64 * NORM_WAVES) void rmsnorm_fwd_kernel(int64_t ro
 
 // dx = dres + r*a - x*r^3*<a,x>/hidden with a = gamma*dh; per-workgroup
 // partial sums of dh*x*r over its rows go to partial[blockIdx.x][hidden].
-// Wave w handles rows w, w+8, w+16, w+24 of the workgroup's 32, each with all
-// its loads (x, dh, dres) issued in one phase; gamma is loaded once.
+// Wave w handles rows w, w+8, .. of the workgroup's rows_per_block, each with
+// all its loads (x, dh, dres) issued in one phase; gamma is loaded once.
 template <int CH>
-__global__ __launch_bounds__(64 * BWD_WAVES) void rmsnorm_bwd_kernel(int64_t rows, int hidden,
+__global__ __launch_bounds__(64 * BWD_WAVES) void rmsnorm_bwd_kernel(int64_t rows, int hidden, int rows_per_block,
                                                                      const bf16_t* __restrict__ x,
                                                                      const bf16_t* __restrict__ gamma,
                                                                      const float* __restrict__ r,
@@ -96,9 +96,9 @@ __global__ __launch_bounds__(64 * BWD_WAVES) void rmsnorm_bwd_kernel(int64_t row
 #pragma unroll
     for (int e = 0; e < 8; ++e) gsum[i][e] = 0.f;
   }
-  const int64_t row_begin = (int64_t)blockIdx.x * BWD_ROWS_PER_BLOCK;
+  const int64_t row_begin = (int64_t)blockIdx.x * rows_per_block;
 #pragma unroll 1
-  for (int rr = wave; rr < BWD_ROWS_PER_BLOCK; rr += BWD_WAVES) {
+  for (int rr = wave; rr < rows_per_block; rr += BWD_WAVES) {
     const int64_t row = row_begin + rr;
     if (row >= rows) break;
     const float rs = r[row];
@@ -289,8 +289,18 @@ hipError_t rmsnorm_fwd(int64_t rows, int hidden, float eps, const bf16_t* x, con
 // More than 8 chunks per lane: one row per wave (rmsnorm_bwd_wide_kernel).
 bool rmsnorm_bwd_wide(int hidden) { return (hidden / 8 + 63) / 64 > 8; }
 
+// Rows per workgroup: as few (in eights, a row per wave) as give at most 256
+// workgroups, so that few rows still spread over the compute units, and at
+// most 32, which keeps the partial rows of the column sum few.  Measured at
+// 2048 x 2048: 64 workgroups of 32 rows 18 us, 256 of 8 rows 9 us.
+int rmsnorm_bwd_rows(int64_t rows, int hidden) {
+  if (rmsnorm_bwd_wide(hidden)) return BWD_WAVES;
+  const int64_t per = BWD_WAVES * ((rows + BWD_WAVES * 256 - 1) / (BWD_WAVES * 256));
+  return per > BWD_MAX_ROWS ? BWD_MAX_ROWS : (int)per;
+}
+
 int rmsnorm_bwd_parts(int64_t rows, int hidden) {
-  const int per = rmsnorm_bwd_wide(hidden) ? BWD_WAVES : BWD_ROWS_PER_BLOCK;
+  const int per = rmsnorm_bwd_rows(rows, hidden);
   return (int)((rows + per - 1) / per);
 }
 
@@ -298,12 +308,12 @@ hipError_t rmsnorm_bwd(int64_t rows, int hidden, const bf16_t* x, const bf16_t* 
                        const bf16_t* dh, const bf16_t* dres, bf16_t* dx, float* dgamma, int accumulate,
                        float* partial, hipStream_t s) {
   const int ch = (hidden / 8 + 63) / 64;
-  const int parts = rmsnorm_bwd_parts(rows, hidden);
+  const int per = rmsnorm_bwd_rows(rows, hidden), parts = rmsnorm_bwd_parts(rows, hidden);
   const dim3 grid((unsigned)parts), block(64 * BWD_WAVES);
 #define LS_B(CHV)                                                                                       \
   case CHV:                                                                                             \
-    hipLaunchKernelGGL((rmsnorm_bwd_kernel<CHV>), grid, block, 0, s, rows, hidden, x, gamma, r, dh, dres, dx, \
-                       partial);                                                                        \
+    hipLaunchKernelGGL((rmsnorm_bwd_kernel<CHV>), grid, block, 0, s, rows, hidden, per, x, gamma, r, dh, dres, \
+                       dx, partial);                                                                    \
     break;
 #define LS_W(CHV)                                                                                            \
   case CHV:                                                                                                  \

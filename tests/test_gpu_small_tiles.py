@@ -106,3 +106,26 @@ def test_mlp_forward_with_and_without_scratch():
         out.append(f64(y))
     # one bf16 unit in the last place (2^-7) where a sum lies at a rounding boundary
     assert np.max(np.abs(out[0] - out[1])) <= 2.0 ** -7 * np.max(np.abs(out[0]))
+
+
+# RMSNorm backward: rows per workgroup 8 (up to 2048 rows), 16, 24 and 32 (from
+# 6145 on; past 8192 more than 256 workgroups), each with a ragged last workgroup
+@pytest.mark.parametrize("rows", [1, 2047, 2049, 4100, 6150, 8300])
+def test_rmsnorm_backward_rows(rows):
+    need_gpu()
+    hidden = 264
+    say(f"rmsnorm backward rows={rows}")
+    x, dh, dres = (bf16_randn((rows, hidden), s) for s in (1, 2, 3))
+    gamma = bf16_randn((hidden,), 4, 0.1) + 1
+    h, r = torch.empty_like(x), torch.empty(rows, dtype=torch.float32, device="cuda")
+    L.ls_rmsnorm_fwd(rows, hidden, 1e-5, x, gamma, h, r)
+    dx, dg = torch.empty_like(x), torch.full((hidden,), 0.5, dtype=torch.float32, device="cuda")
+    ws = torch.empty(L.ls_rmsnorm_bwd_workspace(rows, hidden), dtype=torch.uint8, device="cuda")
+    L.ls_rmsnorm_bwd(rows, hidden, x, gamma, r, dh, dres, dx, dg, True, ws)
+    torch.cuda.synchronize()
+    xf, g, d = f64(x), f64(gamma), f64(dh)
+    rr = 1 / np.sqrt(np.mean(xf * xf, 1, keepdims=True) + 1e-5)
+    ref = f64(dres) + rr * g * d - xf * rr ** 3 * np.sum(g * d * xf, 1, keepdims=True) / hidden
+    assert max_rel(f64(dx), ref) < BF16_TOL
+    # r is fp32 (2^-23) and the column sums add at most 8300 terms of random sign in fp32
+    assert fro_rel(f64(dg) - 0.5, np.sum(d * xf * rr, 0)) < 1e-5
