@@ -118,7 +118,8 @@ int ls_query_sizes(const ls_block_cfg* cfg, ls_sizes* out);
  *   x2 = x + o Wo^T,  o = causal-softmax(q k^T / sqrt(d)) v,
  *   q, k = RoPE(h1 Wq^T), RoPE(h1 Wk^T), v = h1 Wv^T, h1 = RMSNorm(x; attn_norm).
  * x, x2: [batch*seq, hidden] bf16.  attn_saved: opaque, attn_saved bytes
- * (holds h1, rotated q/k, v, o, the RMSNorm scales and the softmax log-sum-exp).
+ * (holds h1, rotated q/k, v, o, the RMSNorm scales, the softmax log-sum-exp and
+ * the RoPE table).
  * x2 must not overlap x or attn_saved. */
 int ls_attn_fwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weights* w,
                 ls_bf16* x2, void* attn_saved, void* workspace, size_t workspace_bytes,

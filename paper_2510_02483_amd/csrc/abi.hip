@@ -180,7 +180,7 @@ struct Carver {
 };
 
 struct AttnSaved {
-  size_t h1, qkv, o, r1, lse, total;
+  size_t h1, qkv, o, r1, lse, rope, total;
 };
 AttnSaved attn_saved_layout(const Dims& m) {
   Carver c;
@@ -190,6 +190,7 @@ AttnSaved attn_saved_layout(const Dims& m) {
   s.o = c.take(m.T * m.Pq * 2);
   s.r1 = c.take(m.T * 4);
   s.lse = c.take(m.B * m.nq * m.S * 4);
+  s.rope = c.take(m.S * m.dp * 4);  // cos and sin, S x dp/2 each
   s.total = c.off;
   return s;
 }
@@ -237,13 +238,12 @@ int64_t max_kpart_floats(std::initializer_list<ls::GemmArgs> products) {
 int64_t glu_cols(const Dims& m) { return 2 * ((m.I + 63) / 64) * 64; }
 
 struct AttnWs {
-  size_t rope, dO, dqkv, dh1, partial, core, wpad, wopad, gpad, gopad, kpart, total;
+  size_t dO, dqkv, dh1, partial, core, wpad, wopad, gpad, gopad, kpart, total;
   int64_t kpart_floats;
 };
 AttnWs attn_ws_layout(const Dims& m) {
   Carver c;
   AttnWs w;
-  w.rope = c.take(m.S * m.dp * 4);  // cos and sin, S x dp/2 each
   w.dO = c.take(m.T * m.Pq * 2);
   w.dqkv = c.take(m.T * m.Pqkv * 2);
   // padded layout only: Wq|Wk|Wv [Pqkv, H] and Wo [H, Pq] in bf16, their fp32 gradients
@@ -371,9 +371,10 @@ PaddedWeights padded_weights(const Dims& m, const ls_block_weights* w, void* ws,
 }
 
 // out_proj = false: stop after the attention core (a recomputation whose x2 is
-// already known).
+// already known).  rope: a table made before (a stack makes one for all its
+// layers); null makes it in the saved state, where the backward pass reads it.
 int run_attn_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const ls_block_weights* w, bf16_t* x2,
-                 void* saved, void* ws, hipStream_t st, bool out_proj = true) {
+                 void* saved, void* ws, const float* rope, hipStream_t st, bool out_proj = true) {
   const AttnSaved sv = attn_saved_layout(m);
   const AttnWs wl = attn_ws_layout(m);
   bf16_t* h1 = at<bf16_t>(saved, sv.h1);
@@ -381,11 +382,13 @@ int run_attn_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
   bf16_t* o = at<bf16_t>(saved, sv.o);
   float* r1 = at<float>(saved, sv.r1);
   float* lse = at<float>(saved, sv.lse);
-  float* cs = at<float>(ws, wl.rope);
+  const float* cs = rope ? rope : at<float>(saved, sv.rope);
   const PaddedWeights pw = padded_weights(m, w, ws, st);
   if (pw.err) return pw.err;
   LS_STEP("rmsnorm fwd", st, ls::rmsnorm_fwd(m.T, (int)m.H, cfg.rms_eps, x, (const bf16_t*)w->attn_norm, h1, r1, st));
-  LS_STEP("rope table", st, ls::rope_table((int)m.S, (int)m.d, (double)cfg.rope_theta, cs, st, (int)m.dp));
+  if (!rope)
+    LS_STEP("rope table", st,
+            ls::rope_table((int)m.S, (int)m.d, (double)cfg.rope_theta, at<float>(saved, sv.rope), st, (int)m.dp));
   ls::GemmArgs g;
   g.M = (int)m.T;
   g.N = (int)m.Pqkv;
@@ -430,7 +433,8 @@ int run_attn_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
 
 int run_attn_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const ls_block_weights* w,
                  const void* saved, const bf16_t* dx2, bf16_t* dx, const ls_block_grads* gr, int accumulate, void* ws,
-                 hipStream_t st) {
+                 const float* rope, hipStream_t st) {
+  (void)cfg;
   const AttnSaved sv = attn_saved_layout(m);
   const AttnWs wl = attn_ws_layout(m);
   const bf16_t* h1 = at<bf16_t>(saved, sv.h1);
@@ -438,7 +442,7 @@ int run_attn_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
   const bf16_t* o = at<bf16_t>(saved, sv.o);
   const float* r1 = at<float>(saved, sv.r1);
   const float* lse = at<float>(saved, sv.lse);
-  float* cs = at<float>(ws, wl.rope);
+  const float* cs = rope ? rope : at<float>(saved, sv.rope);
   bf16_t* dO = at<bf16_t>(ws, wl.dO);
   bf16_t* dqkv = at<bf16_t>(ws, wl.dqkv);
   bf16_t* dh1 = at<bf16_t>(ws, wl.dh1);
@@ -446,7 +450,6 @@ int run_attn_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
   void* core = at<char>(ws, wl.core);
   const PaddedWeights pw = padded_weights(m, w, ws, st);
   if (pw.err) return pw.err;
-  LS_STEP("rope table", st, ls::rope_table((int)m.S, (int)m.d, (double)cfg.rope_theta, cs, st, (int)m.dp));
   {  // dO = dx2 Wo
     ls::GemmArgs g;
     g.M = (int)m.T;
@@ -730,7 +733,7 @@ int64_t logits_rows(const ls_stack_cfg& c) {
 }
 
 struct StackWs {
-  size_t tg, counts, rows, xs, xmid, hf, rf, logits, dh, dxa, dxb, partial, sets, set_stride, dx2, scratch, total;
+  size_t tg, counts, rows, rope, xs, xmid, hf, rf, logits, dh, dxa, dxb, partial, sets, set_stride, dx2, scratch, total;
   size_t asv, msv, x2;  // offsets inside one set
   int64_t head_kpart_floats;  // at the start of scratch
 };
@@ -742,6 +745,7 @@ StackWs stack_ws_layout(const ls_stack_cfg& c) {
   w.tg = k.take(m.T * 4);
   w.counts = k.take(16);
   w.rows = k.take(m.T * 4);
+  w.rope = k.take(m.S * m.dp * 4);
   w.xs = k.take(act * (size_t)(c.n_layers + 1));
   // with recomputation each block's mid-residual x2 is kept too, so that the
   // recomputation stops before the output and down projections
@@ -818,7 +822,8 @@ int ls_attn_fwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weight
   if (int e = check_ranges(in, out)) return e;
   if (workspace_bytes < attn_ws_layout(m).total)
     return fail(LS_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, attn_ws_layout(m).total);
-  return run_attn_fwd(*cfg, m, (const bf16_t*)x, w, (bf16_t*)x2, attn_saved, workspace, (hipStream_t)stream);
+  return run_attn_fwd(*cfg, m, (const bf16_t*)x, w, (bf16_t*)x2, attn_saved, workspace, nullptr,
+                      (hipStream_t)stream);
 }
 
 int ls_attn_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weights* w, const void* attn_saved,
@@ -836,7 +841,7 @@ int ls_attn_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weight
   if (workspace_bytes < attn_ws_layout(m).total)
     return fail(LS_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, attn_ws_layout(m).total);
   return run_attn_bwd(*cfg, m, (const bf16_t*)x, w, attn_saved, (const bf16_t*)dx2, (bf16_t*)dx, g, accumulate != 0,
-                      workspace, (hipStream_t)stream);
+                      workspace, nullptr, (hipStream_t)stream);
 }
 
 int ls_mlp_fwd(const ls_block_cfg* cfg, const ls_bf16* x2, const ls_block_weights* w, ls_bf16* y, void* mlp_saved,
@@ -897,11 +902,11 @@ int ls_block_fwd_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_w
   bf16_t* dx2 = at<bf16_t>(workspace, bl.dx2);
   void* scratch = at<char>(workspace, bl.scratch);
   const int acc = accumulate != 0;
-  if (int e = run_attn_fwd(*cfg, m, (const bf16_t*)x, w, x2, asv, scratch, st)) return e;
+  if (int e = run_attn_fwd(*cfg, m, (const bf16_t*)x, w, x2, asv, scratch, nullptr, st)) return e;
   const MlpWs ml = mlp_ws_layout(m);
   if (int e = run_mlp_fwd(*cfg, m, x2, w, (bf16_t*)y, msv, at<float>(scratch, ml.kpart), ml.kpart_floats, st)) return e;
   if (int e = run_mlp_bwd(*cfg, m, x2, w, msv, (const bf16_t*)dy, dx2, g, acc, scratch, st)) return e;
-  return run_attn_bwd(*cfg, m, (const bf16_t*)x, w, asv, dx2, (bf16_t*)dx, g, acc, scratch, st);
+  return run_attn_bwd(*cfg, m, (const bf16_t*)x, w, asv, dx2, (bf16_t*)dx, g, acc, scratch, nullptr, st);
 }
 
 int ls_timing_begin(const char* label, int max_launches) {
@@ -1221,9 +1226,12 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
   auto x2_of = [&](int l) {
     return cfg->recompute ? at<bf16_t>(workspace, wl.xmid + act * (size_t)l) : at<bf16_t>(set(l), wl.x2);
   };
+  float* rope = at<float>(workspace, wl.rope);
+  if (L > 0)
+    LS_STEP("rope table", st, ls::rope_table((int)m.S, (int)m.d, (double)bc.rope_theta, rope, st, (int)m.dp));
   for (int l = 0; l < L; ++l) {
     char* sv = set(l);
-    if (int e = run_attn_fwd(bc, m, xs(l), &w->layers[l], x2_of(l), sv + wl.asv, scratch, st)) return e;
+    if (int e = run_attn_fwd(bc, m, xs(l), &w->layers[l], x2_of(l), sv + wl.asv, scratch, rope, st)) return e;
     if (int e = run_mlp_fwd(bc, m, x2_of(l), &w->layers[l], xs(l + 1), sv + wl.msv, at<float>(scratch, ml.kpart),
                             ml.kpart_floats, st, !cfg->recompute))
       return e;
@@ -1303,14 +1311,15 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
     char* sv = set(l);
     bf16_t* x2 = x2_of(l);
     if (cfg->recompute) {  // the saved state of both sub-layers; x2 and y are known
-      if (int e = run_attn_fwd(bc, m, xs(l), &w->layers[l], x2, sv + wl.asv, scratch, st, false)) return e;
+      if (int e = run_attn_fwd(bc, m, xs(l), &w->layers[l], x2, sv + wl.asv, scratch, rope, st, false)) return e;
       if (int e = run_mlp_fwd(bc, m, x2, &w->layers[l], nullptr, sv + wl.msv, at<float>(scratch, ml.kpart),
                               ml.kpart_floats, st, true, false))
         return e;
     }
     if (int e = run_mlp_bwd(bc, m, x2, &w->layers[l], sv + wl.msv, dcur, dx2, &g->layers[l], acc, scratch, st))
       return e;
-    if (int e = run_attn_bwd(bc, m, xs(l), &w->layers[l], sv + wl.asv, dx2, dnext, &g->layers[l], acc, scratch, st))
+    if (int e = run_attn_bwd(bc, m, xs(l), &w->layers[l], sv + wl.asv, dx2, dnext, &g->layers[l], acc, scratch, rope,
+                             st))
       return e;
     std::swap(dcur, dnext);
   }
