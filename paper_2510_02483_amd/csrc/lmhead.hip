@@ -137,6 +137,11 @@ __global__ __launch_bounds__(CE_THREADS) void ce_targets_kernel(int64_t T, int S
   }
 }
 
+// The hardware's exp2 (v_exp_f32).  exp2f() adds the scaling that keeps results
+// below 2^-126, five more instructions each; here such a term is nothing next
+// to a row's largest (2^0), and as a gradient it is below bf16's 2^-133 / n.
+LS_DEV float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
+
 LS_DEV float block_max(float v, float* red) {
   v = wave_max(v);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
@@ -217,13 +222,13 @@ __global__ __launch_bounds__(CE_THREADS) void ce_rows_kernel(int V, bf16_t* __re
       if (tid + CE_THREADS * i >= nvec) continue;
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        s += exp2f(fmaf(bf_lo(v[i][e]), kLog2e, -mb)) + exp2f(fmaf(bf_hi(v[i][e]), kLog2e, -mb));
+        s += ex2(fmaf(bf_lo(v[i][e]), kLog2e, -mb)) + ex2(fmaf(bf_hi(v[i][e]), kLog2e, -mb));
     }
   } else {
     for (int c = tid; c < nvec; c += CE_THREADS) {
       const u32x4 w = zv[c];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s += exp2f(fmaf(bf_lo(w[e]), kLog2e, -mb)) + exp2f(fmaf(bf_hi(w[e]), kLog2e, -mb));
+      for (int e = 0; e < 4; ++e) s += ex2(fmaf(bf_lo(w[e]), kLog2e, -mb)) + ex2(fmaf(bf_hi(w[e]), kLog2e, -mb));
     }
   }
   s = block_sum(s, red);
@@ -243,8 +248,8 @@ __global__ __launch_bounds__(CE_THREADS) void ce_rows_kernel(int V, bf16_t* __re
       const int k = 8 * c + 2 * e;
       if (k == g) row_loss[row] = lb * kLn2 - bf_lo(w[e]);
       if (k + 1 == g) row_loss[row] = lb * kLn2 - bf_hi(w[e]);
-      float a = exp2f(fmaf(bf_lo(w[e]), kLog2e, -lb)) - (k == g ? 1.f : 0.f);
-      float b = exp2f(fmaf(bf_hi(w[e]), kLog2e, -lb)) - (k + 1 == g ? 1.f : 0.f);
+      float a = ex2(fmaf(bf_lo(w[e]), kLog2e, -lb)) - (k == g ? 1.f : 0.f);
+      float b = ex2(fmaf(bf_hi(w[e]), kLog2e, -lb)) - (k + 1 == g ? 1.f : 0.f);
       o[e] = bad ? kNan2 : pack_bf2(a * inv_n, b * inv_n);
     }
     return o;
