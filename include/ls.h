@@ -131,7 +131,8 @@ int ls_attn_fwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weight
  * dx2 + (d/dx of the attention branch)^T dx2 and the gradients of attn_norm,
  * wq, wk, wv, wo (other members of *g are ignored and may be NULL).  The
  * backward recomputes the softmax from the saved log-sum-exp.  x and
- * attn_saved must be the ones ls_attn_fwd saw. */
+ * attn_saved must be the ones ls_attn_fwd saw (the RoPE table is read from there,
+ * not made again). */
 int ls_attn_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weights* w,
                 const void* attn_saved, const ls_bf16* dx2, ls_bf16* dx,
                 const ls_block_grads* g, int accumulate, void* workspace,
@@ -140,7 +141,8 @@ int ls_attn_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weight
 /* MLP sub-layer forward (Section 2.4: RMSNorm, SwiGLU):
  *   y = x2 + (silu(h2 Wg^T) * (h2 Wu^T)) Wd^T,  h2 = RMSNorm(x2; mlp_norm).
  * mlp_saved: opaque, mlp_saved bytes (h2, gate and up outputs, their product,
- * the RMSNorm scales). */
+ * the RMSNorm scales).  workspace: of mlp_workspace bytes it lets products of few
+ * tokens split K (partial sums are written there); NULL or less is accepted too. */
 int ls_mlp_fwd(const ls_block_cfg* cfg, const ls_bf16* x2, const ls_block_weights* w,
                ls_bf16* y, void* mlp_saved, void* workspace, size_t workspace_bytes,
                void* stream);
@@ -346,7 +348,7 @@ int ls_embed_bwd(int64_t tokens, int32_t hidden, int32_t vocab, const int32_t* i
 
 /* Tile shape of the matrix products (tuning and testing).  By default every
  * product launch picks its workgroup tile (256 or 192 rows x 256 or 192
- * columns, where its epilogue allows, or 128 x 128) and the split of its K to
+ * columns, where its epilogue allows, 256 x 128 or 128 x 128) and the split of its K to
  * minimise an estimate of its time on the device's compute units.  ls_gemm_tile_override(bm, bn)
  * forces bm x bn (each 256 or 192) for every later launch in the process that
  * allows it (others, and weight gradients that split K, keep 256 x 256);

@@ -2,18 +2,18 @@
 // fp32 accumulation and fused epilogues for the decoder block.
 //
 // One workgroup of 4 waves (one per SIMD, 2 x 2 wave tiles) or 8 waves (two
-// per SIMD, 4 x 2) computes a BM x BN tile of C (256 or 192 on each side);
-// each wave owns up to 16 MFMA blocks of 32x32 with their accumulators in
-// registers.  Operand tiles of 64 k-values move global -> LDS with buffer
-// loads that write LDS directly (16 bytes per lane, no staging registers)
-// and return zero outside the operand, so ragged edges need no branches.  Two
-// LDS stages of about 64 KB: tile k+1 is in flight while the matrix cores
-// consume tile k.
+// per SIMD, 4 x 2) computes a BM x BN tile of C (256 or 192 on each side, 256 x
+// 128, or 128 x 128); each wave owns up to 16 MFMA blocks of 32x32 with their
+// accumulators in registers.  Operand tiles of 64 k-values move global -> LDS
+// with buffer loads that write LDS directly (16 bytes per lane, no staging
+// registers) and return zero outside the operand, so ragged edges need no
+// branches.  The large tiles have two LDS stages of about 64 KB (tile k+1 is in
+// flight while the matrix cores consume tile k), with a third one of B where it
+// fits; 256 x 128 tiles have three stages, 128 x 128 ones four (one workgroup
+// per compute unit) or two (two workgroups).
 //
-// The tile shape is picked per launch: on 256 compute units an 8192 x 3072
-// output is 384 tiles of 256 x 256 (one and a half waves of workgroups) but
-// exactly 512 tiles of 256 x 192, so the launcher estimates waves x tile area
-// for each shape the epilogue allows and takes the smallest.
+// The tile shape and the split of K over workgroups are picked per launch from
+// an estimate of the time of each (make_plan in gemm.hip).
 //
 // The tile depth is set by the load path: a k-contiguous operand row
 // contributes KT*2 bytes per tile, and the buffer->LDS path moves 128-byte row

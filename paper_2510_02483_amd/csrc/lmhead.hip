@@ -137,9 +137,10 @@ __global__ __launch_bounds__(CE_THREADS) void ce_targets_kernel(int64_t T, int S
   }
 }
 
-// The hardware's exp2 (v_exp_f32).  exp2f() adds the scaling that keeps results
-// below 2^-126, five more instructions each; here such a term is nothing next
-// to a row's largest (2^0), and as a gradient it is below bf16's 2^-133 / n.
+// The hardware's exp2 (v_exp_f32), for the sum only.  exp2f() adds the scaling
+// that keeps results below 2^-126, five more instructions each; such a term is
+// nothing next to the row's largest, which is 2^0.  The gradients use exp2f():
+// bf16 holds values down to 2^-133.
 LS_DEV float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 LS_DEV float block_max(float v, float* red) {
@@ -248,8 +249,8 @@ __global__ __launch_bounds__(CE_THREADS) void ce_rows_kernel(int V, bf16_t* __re
       const int k = 8 * c + 2 * e;
       if (k == g) row_loss[row] = lb * kLn2 - bf_lo(w[e]);
       if (k + 1 == g) row_loss[row] = lb * kLn2 - bf_hi(w[e]);
-      float a = ex2(fmaf(bf_lo(w[e]), kLog2e, -lb)) - (k == g ? 1.f : 0.f);
-      float b = ex2(fmaf(bf_hi(w[e]), kLog2e, -lb)) - (k + 1 == g ? 1.f : 0.f);
+      float a = exp2f(fmaf(bf_lo(w[e]), kLog2e, -lb)) - (k == g ? 1.f : 0.f);
+      float b = exp2f(fmaf(bf_hi(w[e]), kLog2e, -lb)) - (k + 1 == g ? 1.f : 0.f);
       o[e] = bad ? kNan2 : pack_bf2(a * inv_n, b * inv_n);
     }
     return o;

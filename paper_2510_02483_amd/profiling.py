@@ -99,7 +99,7 @@ def label_steps(names):
                 lab = "attention fwd"
             elif "attn_bwd" in n:
                 lab = "attention bwd"
-            elif "kpart_reduce_kernel" in n and last in GEMM_ORDER:
+            elif ("kpart_reduce_kernel" in n or "ksplit_finish_kernel" in n) and last in GEMM_ORDER:
                 lab = last
             elif "gemm_kernel" in n and g < len(GEMM_ORDER):
                 lab = GEMM_ORDER[g]
