@@ -129,3 +129,27 @@ def test_rmsnorm_backward_rows(rows):
     assert max_rel(f64(dx), ref) < BF16_TOL
     # r is fp32 (2^-23) and the column sums add at most 8300 terms of random sign in fp32
     assert fro_rel(f64(dg) - 0.5, np.sum(d * xf * rr, 0)) < 1e-5
+
+
+# in registers and streamed (above 131072 columns)
+@pytest.mark.parametrize("V", [264, 131088])
+def test_cross_entropy_smallest_gradients(V):
+    """Probabilities below 2^-126 (exp(-88) to exp(-91)) reach the bf16 gradients, which go down to 2^-133."""
+    need_gpu()
+    say(f"cross-entropy smallest gradients V={V}")
+    z = torch.full((1, V), -88.0, dtype=torch.bfloat16)
+    z[0, 1::2] = -90.0
+    z[0, 2::4] = -91.0
+    z[0, 5] = 0.0
+    p = torch.softmax(z.double(), 1).numpy()
+    p[0, 5] -= 1
+    zc = z.cuda()
+    loss, row = torch.empty(1, device="cuda"), torch.empty(1, device="cuda")
+    ws = torch.empty(L.ls_cross_entropy_workspace(1), dtype=torch.uint8, device="cuda")
+    ids = torch.zeros(1, dtype=torch.int32, device="cuda")
+    L.ls_cross_entropy(zc, 1, ids, torch.full((1,), 5, dtype=torch.int32, device="cuda"), loss, row, ws)
+    torch.cuda.synchronize()
+    got = zc.cpu().double().numpy()
+    # bf16 below 2^-126 steps by 2^-133 (rounding 2^-134), the fp32 exponent (up to 132) is rounded to 2^-17
+    assert np.max(np.abs(got - p)) <= 2.0 ** -134 + 2.0 ** -17 * 2.0 ** -126
+    assert got[0, 0] > 0 and got[0, 1] > 0 and got[0, 2] > 0
