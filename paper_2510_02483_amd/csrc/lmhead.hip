@@ -137,12 +137,14 @@ __global__ __launch_bounds__(CE_THREADS) void ce_targets_kernel(int64_t T, int S
   }
 }
 
-// The hardware's exp2 (v_exp_f32), for the sum only.  exp2f() adds the scaling
-// that keeps results below 2^-126, five more instructions each; such a term is
-// nothing next to the row's largest, which is 2^0.  The gradients use exp2f():
-// bf16 holds values down to 2^-133.  The kernel is bound by vector instructions
-// between its loads and its stores: 4096 rows of 128256 logits 598 -> 542 us,
-// 2048 rows of 32000 67 -> 62 us.
+// The hardware's exp2 (v_exp_f32).  exp2f() adds the scaling that keeps results
+// below 2^-126, five more instructions each; in the sum such a term is nothing
+// next to the row's largest, which is 2^0.  bf16 holds gradients down to 2^-133:
+// eight of them go through exp2f() where one is that small, else v_exp_f32,
+// which is the same there.  The kernel is bound by vector instructions
+// between its loads and its stores: with exp2f() everywhere / in the gradients /
+// so, 4096 rows of 128256 logits take 597 / 542 / 505 us, 2048 rows of 32000
+// 68 / 62 / 56 us.
 LS_DEV float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 LS_DEV float block_max(float v, float* red) {
@@ -245,14 +247,28 @@ __global__ __launch_bounds__(CE_THREADS) void ce_rows_kernel(int V, bf16_t* __re
   // the thread holding z[target] writes the row's loss
   if (bad && tid == 0) row_loss[row] = NAN;
   auto grad = [&](u32x4 w, int c) {
-    u32x4 o;
+    float t[8];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int k = 8 * c + 2 * e;
       if (k == g) row_loss[row] = lb * kLn2 - bf_lo(w[e]);
       if (k + 1 == g) row_loss[row] = lb * kLn2 - bf_hi(w[e]);
-      float a = exp2f(fmaf(bf_lo(w[e]), kLog2e, -lb)) - (k == g ? 1.f : 0.f);
-      float b = exp2f(fmaf(bf_hi(w[e]), kLog2e, -lb)) - (k + 1 == g ? 1.f : 0.f);
+      t[2 * e] = fmaf(bf_lo(w[e]), kLog2e, -lb);
+      t[2 * e + 1] = fmaf(bf_hi(w[e]), kLog2e, -lb);
+    }
+    const float lo = fminf(fminf(fminf(t[0], t[1]), fminf(t[2], t[3])), fminf(fminf(t[4], t[5]), fminf(t[6], t[7])));
+    if (lo >= -126.f) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t[e] = ex2(t[e]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) t[e] = exp2f(t[e]);
+    }
+    u32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = 8 * c + 2 * e;
+      const float a = t[2 * e] - (k == g ? 1.f : 0.f), b = t[2 * e + 1] - (k + 1 == g ? 1.f : 0.f);
       o[e] = bad ? kNan2 : pack_bf2(a * inv_n, b * inv_n);
     }
     return o;
