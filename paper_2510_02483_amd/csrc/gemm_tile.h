@@ -295,6 +295,14 @@ LS_DEV void store_resid8(const GemmArgs& p, int m, int n, float v[8]) {
   for (int e = 0; e < 8; ++e) v[e] += r[e];
   *(u32x4*)(p.C + (int64_t)m * p.ldc + n) = pack8f(v);
 }
+// The rotation of a pair (x1, x2) of a head's halves.  The fused operations are
+// spelled out: left to the compiler, the 256 x 256 and the 128-column tiles
+// fused different products of hi, so that one value of q and k in 100000
+// depended on the tile shape by a rounding.
+LS_DEV void rope_rotate(float x1, float x2, float c, float s, float& lo, float& hi) {
+  lo = fmaf(x1, c, -(x2 * s));
+  hi = fmaf(x1, s, x2 * c);
+}
 // columns n (first half of a head) and n + HD/2
 template <int HD>
 LS_DEV void store_rope8(const GemmArgs& p, int m, int n, float a[8], float b[8]) {
@@ -307,9 +315,7 @@ LS_DEV void store_rope8(const GemmArgs& p, int m, int n, float a[8], float b[8])
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float c = e < 4 ? c0[e & 3] : c1[e & 3], s = e < 4 ? s0[e & 3] : s1[e & 3];
-      const float x1 = a[e], x2 = b[e];
-      a[e] = x1 * c - x2 * s;
-      b[e] = x2 * c + x1 * s;
+      rope_rotate(a[e], b[e], c, s, a[e], b[e]);
     }
   }
   bf16_t* dst = p.C + (int64_t)m * p.ldc + n;
@@ -984,10 +990,7 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
             for (int e = 0; e < 4; ++e) {
               const float x1 = acc[i][j][4 * q + e];
               if (rot && j + JP < TN) {
-                const float c = c4[e], sv = s4[e];
-                const float x2 = acc[i][(j + JP) % TN][4 * q + e];
-                lo[e] = x1 * c - x2 * sv;
-                hi[e] = x2 * c + x1 * sv;
+                rope_rotate(x1, acc[i][(j + JP) % TN][4 * q + e], c4[e], s4[e], lo[e], hi[e]);
               } else {
                 lo[e] = x1;
               }

@@ -108,6 +108,38 @@ def test_mlp_forward_with_and_without_scratch():
     assert np.max(np.abs(out[0] - out[1])) <= 2.0 ** -7 * np.max(np.abs(out[0]))
 
 
+# q/k/v projections that take 256 x 128 tiles (K = 256: unsplit) or, forced, 256 x 256
+ROPE_D128 = configs.BlockConfig("rope-d128", 33, batch=2, seq=1030, hidden=256, n_q_heads=16, n_kv_heads=2, head_dim=128,
+                                intermediate=264, rope_theta=1e4)
+ROPE_D64 = configs.BlockConfig("rope-d64", 34, batch=2, seq=1030, hidden=256, n_q_heads=24, n_kv_heads=8, head_dim=64,
+                               intermediate=264, rope_theta=1e4)
+
+
+@pytest.mark.parametrize("c", [ROPE_D128, ROPE_D64], ids=lambda c: c.name)
+def test_rope_does_not_depend_on_the_tile(c):
+    """Unsplit products sum K in the same order in every tile shape, and the rotation rounds
+    the same way in every epilogue: the saved state (q, k, v, o) is the same bit for bit."""
+    need_gpu()
+    say(f"rope by tile shape {c.name}")
+    host = inputs.make_inputs(c, gamma="random")
+    w = {n: host[n].cuda() for n in L.WEIGHTS}
+    x = host["x"].cuda().view(c.tokens, c.hidden)
+    sizes = L.ls_query_sizes(c)
+    got = []
+    try:
+        for tile in ((0, 0), (256, 256)):
+            L.ls_gemm_tile_override(*tile)
+            y = torch.empty_like(x)
+            saved = torch.zeros(sizes["attn_saved"], dtype=torch.uint8, device="cuda")
+            L.ls_attn_fwd(c, x, w, y, saved, torch.empty(sizes["attn_workspace"], dtype=torch.uint8, device="cuda"))
+            torch.cuda.synchronize()
+            got.append((saved, y))
+    finally:
+        L.ls_gemm_tile_override(0, 0)
+    assert torch.equal(got[0][0], got[1][0])
+    assert torch.equal(got[0][1], got[1][1])
+
+
 # RMSNorm backward: rows per workgroup 8 (up to 2048 rows), 16, 24 and 32 (from
 # 6145 on; past 8192 more than 256 workgroups), each with a ragged last workgroup
 @pytest.mark.parametrize("rows", [1, 2047, 2049, 4100, 6150, 8300])
