@@ -292,6 +292,8 @@ MlpWs mlp_ws_layout(const Dims& m) {
 
 struct BlockWs {
   size_t attn_saved, mlp_saved, x2, dx2, scratch, total;
+  AttnWs attn;  // inside scratch
+  MlpWs mlp;
 };
 BlockWs block_ws_layout(const Dims& m) {
   Carver c;
@@ -300,7 +302,9 @@ BlockWs block_ws_layout(const Dims& m) {
   w.mlp_saved = c.take(mlp_saved_layout(m).total);
   w.x2 = c.take(m.T * m.H * 2);
   w.dx2 = c.take(m.T * m.H * 2);
-  w.scratch = c.take(std::max(attn_ws_layout(m).total, mlp_ws_layout(m).total));
+  w.attn = attn_ws_layout(m);
+  w.mlp = mlp_ws_layout(m);
+  w.scratch = c.take(std::max(w.attn.total, w.mlp.total));
   w.total = c.off;
   return w;
 }
@@ -349,6 +353,9 @@ void grad_ranges(const Dims& m, const ls_block_grads* g, bool attn, bool mlp, st
 }
 
 // ---- the sub-layers (arguments already checked) ------------------------------------
+//
+// wl: the layout of the scratch at ws that the entry point has checked the
+// caller's workspace against, computed once per call.
 
 // The projection weights in the layout the attention kernels read: the
 // caller's buffers, or (padded head layout) copies in the workspace.
@@ -356,9 +363,8 @@ struct PaddedWeights {
   const bf16_t *wq, *wk, *wv, *wo;
   int err;
 };
-PaddedWeights padded_weights(const Dims& m, const ls_block_weights* w, void* ws, hipStream_t st) {
+PaddedWeights padded_weights(const Dims& m, const ls_block_weights* w, void* ws, const AttnWs& wl, hipStream_t st) {
   if (!m.pad) return {(const bf16_t*)w->wq, (const bf16_t*)w->wk, (const bf16_t*)w->wv, (const bf16_t*)w->wo, LS_OK};
-  const AttnWs wl = attn_ws_layout(m);
   bf16_t* wp = at<bf16_t>(ws, wl.wpad);
   bf16_t* wo = at<bf16_t>(ws, wl.wopad);
   const int d = (int)m.d, dp = (int)m.dp, H = (int)m.H;
@@ -374,16 +380,15 @@ PaddedWeights padded_weights(const Dims& m, const ls_block_weights* w, void* ws,
 // already known).  rope: a table made before (a stack makes one for all its
 // layers); null makes it in the saved state, where the backward pass reads it.
 int run_attn_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const ls_block_weights* w, bf16_t* x2,
-                 void* saved, void* ws, const float* rope, hipStream_t st, bool out_proj = true) {
+                 void* saved, void* ws, const AttnWs& wl, const float* rope, hipStream_t st, bool out_proj = true) {
   const AttnSaved sv = attn_saved_layout(m);
-  const AttnWs wl = attn_ws_layout(m);
   bf16_t* h1 = at<bf16_t>(saved, sv.h1);
   bf16_t* qkv = at<bf16_t>(saved, sv.qkv);
   bf16_t* o = at<bf16_t>(saved, sv.o);
   float* r1 = at<float>(saved, sv.r1);
   float* lse = at<float>(saved, sv.lse);
   const float* cs = rope ? rope : at<float>(saved, sv.rope);
-  const PaddedWeights pw = padded_weights(m, w, ws, st);
+  const PaddedWeights pw = padded_weights(m, w, ws, wl, st);
   if (pw.err) return pw.err;
   LS_STEP("rmsnorm fwd", st, ls::rmsnorm_fwd(m.T, (int)m.H, cfg.rms_eps, x, (const bf16_t*)w->attn_norm, h1, r1, st));
   if (!rope)
@@ -433,10 +438,9 @@ int run_attn_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
 
 int run_attn_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const ls_block_weights* w,
                  const void* saved, const bf16_t* dx2, bf16_t* dx, const ls_block_grads* gr, int accumulate, void* ws,
-                 const float* rope, hipStream_t st) {
+                 const AttnWs& wl, const float* rope, hipStream_t st) {
   (void)cfg;
   const AttnSaved sv = attn_saved_layout(m);
-  const AttnWs wl = attn_ws_layout(m);
   const bf16_t* h1 = at<bf16_t>(saved, sv.h1);
   const bf16_t* qkv = at<bf16_t>(saved, sv.qkv);
   const bf16_t* o = at<bf16_t>(saved, sv.o);
@@ -448,7 +452,7 @@ int run_attn_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
   bf16_t* dh1 = at<bf16_t>(ws, wl.dh1);
   float* partial = at<float>(ws, wl.partial);
   void* core = at<char>(ws, wl.core);
-  const PaddedWeights pw = padded_weights(m, w, ws, st);
+  const PaddedWeights pw = padded_weights(m, w, ws, wl, st);
   if (pw.err) return pw.err;
   {  // dO = dx2 Wo
     ls::GemmArgs g;
@@ -610,10 +614,9 @@ int run_mlp_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x2, const 
 
 int run_mlp_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x2, const ls_block_weights* w,
                 const void* saved, const bf16_t* dy, bf16_t* dx2, const ls_block_grads* gr, int accumulate, void* ws,
-                hipStream_t st) {
+                const MlpWs& wl, hipStream_t st) {
   (void)cfg;
   const MlpSaved sv = mlp_saved_layout(m);
-  const MlpWs wl = mlp_ws_layout(m);
   const bf16_t* h2 = at<bf16_t>(saved, sv.h2);
   const bf16_t* gu = at<bf16_t>(saved, sv.gu);
   const bf16_t* act = at<bf16_t>(saved, sv.act);
@@ -735,6 +738,8 @@ int64_t logits_rows(const ls_stack_cfg& c) {
 struct StackWs {
   size_t tg, counts, rows, rope, xs, xmid, hf, rf, logits, dh, dxa, dxb, partial, sets, set_stride, dx2, scratch, total;
   size_t asv, msv, x2;  // offsets inside one set
+  AttnWs attn;                // inside scratch
+  MlpWs mlp;
   int64_t head_kpart_floats;  // at the start of scratch
 };
 StackWs stack_ws_layout(const ls_stack_cfg& c) {
@@ -763,7 +768,9 @@ StackWs stack_ws_layout(const ls_stack_cfg& c) {
       product(ls::EPI_BF16, true, false, logits_rows(c), m.H, c.vocab),  // dh head
       product(ls::EPI_F32, false, false, c.vocab, m.H, logits_rows(c)),  // dE head
   });
-  w.scratch = k.take(std::max({attn_ws_layout(m).total, mlp_ws_layout(m).total, (size_t)w.head_kpart_floats * 4}));
+  w.attn = attn_ws_layout(m);
+  w.mlp = mlp_ws_layout(m);
+  w.scratch = k.take(std::max({w.attn.total, w.mlp.total, (size_t)w.head_kpart_floats * 4}));
   Carver one;
   w.asv = one.take(attn_saved_layout(m).total);
   w.msv = one.take(mlp_saved_layout(m).total);
@@ -820,9 +827,10 @@ int ls_attn_fwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weight
                                            {workspace, workspace_bytes, "workspace"}};
   weight_ranges(m, w, true, false, in);
   if (int e = check_ranges(in, out)) return e;
-  if (workspace_bytes < attn_ws_layout(m).total)
-    return fail(LS_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, attn_ws_layout(m).total);
-  return run_attn_fwd(*cfg, m, (const bf16_t*)x, w, (bf16_t*)x2, attn_saved, workspace, nullptr,
+  const AttnWs wl = attn_ws_layout(m);
+  if (workspace_bytes < wl.total)
+    return fail(LS_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, wl.total);
+  return run_attn_fwd(*cfg, m, (const bf16_t*)x, w, (bf16_t*)x2, attn_saved, workspace, wl, nullptr,
                       (hipStream_t)stream);
 }
 
@@ -838,10 +846,11 @@ int ls_attn_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weight
   weight_ranges(m, w, true, false, in);
   grad_ranges(m, g, true, false, out);
   if (int e = check_ranges(in, out)) return e;
-  if (workspace_bytes < attn_ws_layout(m).total)
-    return fail(LS_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, attn_ws_layout(m).total);
+  const AttnWs wl = attn_ws_layout(m);
+  if (workspace_bytes < wl.total)
+    return fail(LS_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, wl.total);
   return run_attn_bwd(*cfg, m, (const bf16_t*)x, w, attn_saved, (const bf16_t*)dx2, (bf16_t*)dx, g, accumulate != 0,
-                      workspace, nullptr, (hipStream_t)stream);
+                      workspace, wl, nullptr, (hipStream_t)stream);
 }
 
 int ls_mlp_fwd(const ls_block_cfg* cfg, const ls_bf16* x2, const ls_block_weights* w, ls_bf16* y, void* mlp_saved,
@@ -874,10 +883,11 @@ int ls_mlp_bwd(const ls_block_cfg* cfg, const ls_bf16* x2, const ls_block_weight
   weight_ranges(m, w, false, true, in);
   grad_ranges(m, g, false, true, out);
   if (int e = check_ranges(in, out)) return e;
-  if (workspace_bytes < mlp_ws_layout(m).total)
-    return fail(LS_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, mlp_ws_layout(m).total);
+  const MlpWs wl = mlp_ws_layout(m);
+  if (workspace_bytes < wl.total)
+    return fail(LS_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, wl.total);
   return run_mlp_bwd(*cfg, m, (const bf16_t*)x2, w, mlp_saved, (const bf16_t*)dy, (bf16_t*)dx2, g, accumulate != 0,
-                     workspace, (hipStream_t)stream);
+                     workspace, wl, (hipStream_t)stream);
 }
 
 int ls_block_fwd_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weights* w, const ls_bf16* dy,
@@ -902,11 +912,11 @@ int ls_block_fwd_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_w
   bf16_t* dx2 = at<bf16_t>(workspace, bl.dx2);
   void* scratch = at<char>(workspace, bl.scratch);
   const int acc = accumulate != 0;
-  if (int e = run_attn_fwd(*cfg, m, (const bf16_t*)x, w, x2, asv, scratch, nullptr, st)) return e;
-  const MlpWs ml = mlp_ws_layout(m);
-  if (int e = run_mlp_fwd(*cfg, m, x2, w, (bf16_t*)y, msv, at<float>(scratch, ml.kpart), ml.kpart_floats, st)) return e;
-  if (int e = run_mlp_bwd(*cfg, m, x2, w, msv, (const bf16_t*)dy, dx2, g, acc, scratch, st)) return e;
-  return run_attn_bwd(*cfg, m, (const bf16_t*)x, w, asv, dx2, (bf16_t*)dx, g, acc, scratch, nullptr, st);
+  if (int e = run_attn_fwd(*cfg, m, (const bf16_t*)x, w, x2, asv, scratch, bl.attn, nullptr, st)) return e;
+  if (int e = run_mlp_fwd(*cfg, m, x2, w, (bf16_t*)y, msv, at<float>(scratch, bl.mlp.kpart), bl.mlp.kpart_floats, st))
+    return e;
+  if (int e = run_mlp_bwd(*cfg, m, x2, w, msv, (const bf16_t*)dy, dx2, g, acc, scratch, bl.mlp, st)) return e;
+  return run_attn_bwd(*cfg, m, (const bf16_t*)x, w, asv, dx2, (bf16_t*)dx, g, acc, scratch, bl.attn, nullptr, st);
 }
 
 int ls_timing_begin(const char* label, int max_launches) {
@@ -1218,7 +1228,6 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
   bf16_t* dxb = at<bf16_t>(workspace, wl.dxb);
   bf16_t* dx2 = at<bf16_t>(workspace, wl.dx2);
   void* scratch = at<char>(workspace, wl.scratch);
-  const MlpWs ml = mlp_ws_layout(m);
 
   // forward: embedding, blocks (keeping every block's input), final norm
   LS_STEP("embedding fwd", st, ls::embed_fwd(m.T, (int)m.H, (int)V, ids, E, xs(0), st));
@@ -1231,9 +1240,9 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
     LS_STEP("rope table", st, ls::rope_table((int)m.S, (int)m.d, (double)bc.rope_theta, rope, st, (int)m.dp));
   for (int l = 0; l < L; ++l) {
     char* sv = set(l);
-    if (int e = run_attn_fwd(bc, m, xs(l), &w->layers[l], x2_of(l), sv + wl.asv, scratch, rope, st)) return e;
-    if (int e = run_mlp_fwd(bc, m, x2_of(l), &w->layers[l], xs(l + 1), sv + wl.msv, at<float>(scratch, ml.kpart),
-                            ml.kpart_floats, st, !cfg->recompute))
+    if (int e = run_attn_fwd(bc, m, xs(l), &w->layers[l], x2_of(l), sv + wl.asv, scratch, wl.attn, rope, st)) return e;
+    if (int e = run_mlp_fwd(bc, m, x2_of(l), &w->layers[l], xs(l + 1), sv + wl.msv, at<float>(scratch, wl.mlp.kpart),
+                            wl.mlp.kpart_floats, st, !cfg->recompute))
       return e;
   }
   LS_STEP("rmsnorm fwd", st,
@@ -1311,15 +1320,16 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
     char* sv = set(l);
     bf16_t* x2 = x2_of(l);
     if (cfg->recompute) {  // the saved state of both sub-layers; x2 and y are known
-      if (int e = run_attn_fwd(bc, m, xs(l), &w->layers[l], x2, sv + wl.asv, scratch, rope, st, false)) return e;
-      if (int e = run_mlp_fwd(bc, m, x2, &w->layers[l], nullptr, sv + wl.msv, at<float>(scratch, ml.kpart),
-                              ml.kpart_floats, st, true, false))
+      if (int e = run_attn_fwd(bc, m, xs(l), &w->layers[l], x2, sv + wl.asv, scratch, wl.attn, rope, st, false))
+        return e;
+      if (int e = run_mlp_fwd(bc, m, x2, &w->layers[l], nullptr, sv + wl.msv, at<float>(scratch, wl.mlp.kpart),
+                              wl.mlp.kpart_floats, st, true, false))
         return e;
     }
-    if (int e = run_mlp_bwd(bc, m, x2, &w->layers[l], sv + wl.msv, dcur, dx2, &g->layers[l], acc, scratch, st))
+    if (int e = run_mlp_bwd(bc, m, x2, &w->layers[l], sv + wl.msv, dcur, dx2, &g->layers[l], acc, scratch, wl.mlp, st))
       return e;
-    if (int e = run_attn_bwd(bc, m, xs(l), &w->layers[l], sv + wl.asv, dx2, dnext, &g->layers[l], acc, scratch, rope,
-                             st))
+    if (int e = run_attn_bwd(bc, m, xs(l), &w->layers[l], sv + wl.asv, dx2, dnext, &g->layers[l], acc, scratch, wl.attn,
+                             rope, st))
       return e;
     std::swap(dcur, dnext);
   }

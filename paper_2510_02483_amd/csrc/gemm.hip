@@ -169,7 +169,8 @@ int64_t kpart_need(const GemmArgs& a, int ks) {
   return ks <= 1 ? 0 : (int64_t)(a.epi == EPI_F32 ? ks - 1 : ks) * a.M * a.N;
 }
 
-Plan make_plan(const GemmArgs& a, int64_t kpart_floats) {
+// forced: 0, or the tile shape of ls_gemm_tile_override (1000 BM + BN).
+Plan make_plan(const GemmArgs& a, int64_t kpart_floats, int forced) {
   const bool nt = a.a_kcontig && a.b_kcontig, f32 = a.epi == EPI_F32;
   // 192-wide tiles of a k-contiguous B put a wave's blocks in two 64-row segments: one buffer only
   const bool n192 = nt ? (a.epi == EPI_BF16 || a.epi == EPI_RESID) && a.b_start[1] >= a.N : a.epi != EPI_GLU_BWD;
@@ -177,7 +178,7 @@ Plan make_plan(const GemmArgs& a, int64_t kpart_floats) {
   const int ncu = compute_units();
   const int64_t ktiles = ((int64_t)a.K + KT - 1) / KT;
   Plan best;
-  if (const int forced = g_tile_override.load(std::memory_order_relaxed)) {
+  if (forced) {
     const int bm = forced / 1000, bn = forced % 1000;
     if ((bm == 256 || m192) && (bn == 256 || n192)) {
       best.bm = bm;
@@ -247,8 +248,11 @@ int gemm_tile_override(int bm, int bn) {
   return 0;
 }
 
+// Workspace sizes come from this, so it does not look at the tile override: a
+// workspace serves every setting, and one switched by another thread during a
+// call cannot make a launch need more than the call has checked.
 int64_t gemm_kpart_floats(const GemmArgs& a) {
-  int64_t need = kpart_need(a, make_plan(a, INT64_MAX).ks);
+  int64_t need = kpart_need(a, make_plan(a, INT64_MAX, 0).ks);
   // the split a forced tile shape would use
   if (a.epi == EPI_F32) need = std::max(need, kpart_need(a, ksplit_of(a.M, a.N, a.K)));
   return need;
@@ -261,7 +265,7 @@ hipError_t gemm(const GemmArgs& args, hipStream_t s) {
   if (a.b_kcontig && ((a.b_start[1] % 64 && a.b_start[1] < a.N) || (a.b_start[2] % 64 && a.b_start[2] < a.N)))
     return hipErrorInvalidValue;
   if (!a.a_kcontig && a.b_kcontig) return hipErrorInvalidValue;
-  const Plan p = make_plan(a, a.kpart ? a.kpart_floats : 0);
+  const Plan p = make_plan(a, a.kpart ? a.kpart_floats : 0, g_tile_override.load(std::memory_order_relaxed));
   a.ksplit = p.ks;
   a.group_m = group_rows(a.M, a.N, a.K, p.bm, p.bn);
   const GemmTile t = p.bm == 128 ? (p.deep ? TILE_128_DEEP : TILE_128)

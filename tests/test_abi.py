@@ -131,6 +131,25 @@ def test_gemm_tile_override_arguments():
     assert lib.ls_gemm_tile_override(0, 0) == 0
 
 
+def test_workspace_sizes_do_not_depend_on_the_tile_override():
+    """A workspace of any size query serves calls under every tile setting: the
+    sizes are those of the configuration alone.  Shapes whose bf16 products split
+    K (few tokens; 2048 tokens of the report's 3B block) among them."""
+    lib = L.lib()
+    blocks = [configs.TINY, configs.PAPER_3B.with_(batch=1, seq=2048), configs.B3, configs.PAPER_30B,
+              configs.TINY.with_(batch=1, seq=72, hidden=4104, n_q_heads=4, head_dim=128, intermediate=4616)]
+    stacks = [configs.TINY_STACK, configs.TINY_STACK.with_(vocab=32000, block=blocks[1], recompute=True)]
+    query = lambda: [L.ls_query_sizes(c) for c in blocks] + [L.ls_stack_workspace(sc) for sc in stacks]  # noqa: E731
+    want = query()
+    try:
+        for bm in (256, 192):
+            for bn in (256, 192):
+                assert lib.ls_gemm_tile_override(bm, bn) == 0
+                assert query() == want, (bm, bn)
+    finally:
+        lib.ls_gemm_tile_override(0, 0)
+
+
 def _stack_args(sc, L_=None):
     """Fake, disjoint, aligned device addresses for every stack argument (the
     checks run before any HIP call, so nothing is dereferenced)."""
