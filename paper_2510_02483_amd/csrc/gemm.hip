@@ -87,6 +87,8 @@ int compute_units() {
   return n;
 }
 
+constexpr int64_t LLC_BYTES = (int64_t)256 << 20;  // last-level cache
+
 // Tile rows per group of the launch order (map_tile) for an M x N x K product
 // in BM x BN tiles.  Two caches decide it.  The workgroups an XCD runs at once
 // (one per CU, 32) cover g tile rows x 32/g tile columns and stream g A panels
@@ -100,7 +102,6 @@ int compute_units() {
 int group_rows(int M, int N, int K, int bm, int bn) {
   const int tiles_m = (M + bm - 1) / bm, tiles_n = (N + bn - 1) / bn;
   const int ncu = compute_units(), round = std::min(tiles_m * tiles_n, ncu), per_xcd = std::max(ncu / 8, 1);
-  constexpr int64_t LLC_BYTES = (int64_t)256 << 20;
   constexpr int MAX_TILES = 4096;  // per dimension (no allocation in a call): larger grids keep 8
   if (tiles_m > MAX_TILES || tiles_n > MAX_TILES) return 8;
   int best = 8;
@@ -148,6 +149,15 @@ std::atomic<int> g_tile_override{0};  // 0: automatic, else 1000 * BM + BN
 // x 22016 327 -> 169 us (256 workgroups where there were 88), 504 x 3072 x 8192
 // 106 -> 37 us (two slices), 2048 x 2560 x 2048 36 -> 28 us, 256 x 512 x 256
 // 10 -> 6 us; 8192 x 16384 x 3072 stays 256 x 256 (620 us against 760 with 128 x 128).
+//
+// Partial sums are held to the size of the last-level cache.  They are the
+// caller's workspace, and beyond the cache they go to memory and back, which
+// leaves little of the gain: 8192 x 6656 x 35840 in three slices (624 MiB,
+// doubling the MLP's workspace) 3317 us against 3410 unsplit, 4096 rows of it
+// (312 MiB) 1560 against 1648.  Within it: 9536 x 2560 x 24816 in two slices
+// (186 MiB) 1159 against 1396, 4864 x 3400 x 28544 in four (252 MiB) 932 against
+// 1017; 5190 x 3328 x 27264 906 in three (198 MiB), 880 in four (264 MiB), 931
+// unsplit.
 struct Plan {
   int bm = 256, bn = 256, ks = 1;
   bool deep = true;  // 128 x 128: four stages, one workgroup per CU
@@ -191,7 +201,7 @@ Plan make_plan(const GemmArgs& a, int64_t kpart_floats, int forced) {
   }
   double best_us = 0.0;
   auto consider = [&](int bm, int bn, int ks) {
-    if (kpart_need(a, ks) > kpart_floats) return;
+    if (kpart_need(a, ks) > std::min(kpart_floats, LLC_BYTES / 4)) return;
     const int64_t wgs = (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * ks;
     const double kt = (double)((ktiles + ks - 1) / ks);
     Plan p;

@@ -150,6 +150,16 @@ def test_workspace_sizes_do_not_depend_on_the_tile_override():
         lib.ls_gemm_tile_override(0, 0)
 
 
+@pytest.mark.parametrize("c", [configs.PAPER_30B, configs.B30, configs.PAPER_3B, configs.B3.with_(batch=1, seq=500)],
+                         ids=lambda c: f"{c.name}-{c.tokens}")
+def test_partial_sums_fit_the_last_level_cache(c):
+    """What the MLP's scratch holds beside the gradients of its activations and the norm's partial
+    rows is the partial sums of products that split K: at most 256 MiB."""
+    T, H, I = c.tokens, c.hidden, c.intermediate
+    rest = 2 * T * 2 * I + 2 * T * H + L.lib().ls_rmsnorm_bwd_workspace(T, H) + 4 * 256
+    assert L.ls_query_sizes(c)["mlp_workspace"] <= rest + (256 << 20)
+
+
 def _stack_args(sc, L_=None):
     """Fake, disjoint, aligned device addresses for every stack argument (the
     checks run before any HIP call, so nothing is dereferenced)."""
