@@ -215,27 +215,52 @@ ls::AttnShape attn_shape(const Dims& m) {
   return ls::AttnShape{(int)m.B, (int)m.S, (int)m.nq, (int)m.nkv, (int)m.dp, (int)m.d};
 }
 
-// Floats of fp32 partial sums for the products that split K (their output
-// tiles alone would leave most compute units idle): the most any of the
-// products named needs.  Only what the choice of tile depends on is set.
-ls::GemmArgs product(int epi, bool a_kcontig, bool b_kcontig, int64_t M, int64_t N, int64_t K, int64_t b_start1 = 1 << 30) {
+// The matrix products of a call, by their LS_STEP labels: what the choice of
+// tile and split depends on.  The workspace holds the fp32 partial sums of the
+// one that needs the most (output tiles alone would leave most compute units
+// idle where K is split).
+struct Product {
+  const char* label;
   ls::GemmArgs g;
-  g.epi = epi;
-  g.a_kcontig = a_kcontig;
-  g.b_kcontig = b_kcontig;
-  g.M = (int)M;
-  g.N = (int)N;
-  g.K = (int)K;
-  g.b_start[1] = (int)b_start1;
-  return g;
+};
+Product product(const char* label, int epi, bool a_kcontig, bool b_kcontig, int64_t M, int64_t N, int64_t K,
+                int64_t b_start1 = 1 << 30) {
+  Product p;
+  p.label = label;
+  p.g.epi = epi;
+  p.g.a_kcontig = a_kcontig;
+  p.g.b_kcontig = b_kcontig;
+  p.g.M = (int)M;
+  p.g.N = (int)N;
+  p.g.K = (int)K;
+  p.g.b_start[1] = (int)b_start1;
+  return p;
 }
-int64_t max_kpart_floats(std::initializer_list<ls::GemmArgs> products) {
+template <size_t N>
+int64_t max_kpart_floats(const std::array<Product, N>& products) {
   int64_t n = 0;
-  for (const ls::GemmArgs& g : products) n = std::max(n, ls::gemm_kpart_floats(g));
+  for (const Product& p : products) n = std::max(n, ls::gemm_kpart_floats(p.g));
   return n;
 }
 // Columns of the gate/up product: whole 64-feature blocks of gate and up.
 int64_t glu_cols(const Dims& m) { return 2 * ((m.I + 63) / 64) * 64; }
+
+std::array<Product, 6> attn_products(const Dims& m) {
+  return {product("qkv projection", ls::EPI_ROPE, true, true, m.T, m.Pqkv, m.H, m.Pq),
+          product("output projection", ls::EPI_RESID, true, true, m.T, m.H, m.Pq),
+          product("dO", ls::EPI_BF16, true, false, m.T, m.Pq, m.H),
+          product("dh1", ls::EPI_BF16, true, false, m.T, m.H, m.Pqkv),
+          product("dWo", ls::EPI_F32, false, false, m.H, m.Pq, m.T),
+          product("dWqkv", ls::EPI_F32, false, false, m.Pqkv, m.H, m.T)};
+}
+std::array<Product, 6> mlp_products(const Dims& m) {
+  return {product("gate/up projection", ls::EPI_GLU_FWD, true, true, m.T, glu_cols(m), m.H),
+          product("down projection", ls::EPI_RESID, true, true, m.T, m.H, m.I),
+          product("dact", ls::EPI_GLU_BWD, true, false, m.T, m.I, m.H),
+          product("dh2", ls::EPI_BF16, true, false, m.T, m.H, 2 * m.I, m.I),
+          product("dWg/dWu", ls::EPI_F32, false, false, 2 * m.I, m.H, m.T),
+          product("dWd", ls::EPI_F32, false, false, m.H, m.I, m.T)};
+}
 
 struct AttnWs {
   size_t dO, dqkv, dh1, partial, core, wpad, wopad, gpad, gopad, kpart, total;
@@ -254,14 +279,7 @@ AttnWs attn_ws_layout(const Dims& m) {
   w.dh1 = c.take(m.T * m.H * 2);
   w.partial = c.take(norm_partial_bytes(m));
   w.core = c.take(ls::attn_bwd_workspace(attn_shape(m)));
-  w.kpart_floats = max_kpart_floats({
-      product(ls::EPI_ROPE, true, true, m.T, m.Pqkv, m.H, m.Pq),  // q/k/v projection
-      product(ls::EPI_RESID, true, true, m.T, m.H, m.Pq),         // output projection
-      product(ls::EPI_BF16, true, false, m.T, m.Pq, m.H),         // dO
-      product(ls::EPI_BF16, true, false, m.T, m.H, m.Pqkv),       // dh1
-      product(ls::EPI_F32, false, false, m.H, m.Pq, m.T),         // dWo
-      product(ls::EPI_F32, false, false, m.Pqkv, m.H, m.T),       // dWqkv
-  });
+  w.kpart_floats = max_kpart_floats(attn_products(m));
   w.kpart = c.take((size_t)w.kpart_floats * 4);
   w.total = c.off;
   return w;
@@ -277,14 +295,7 @@ MlpWs mlp_ws_layout(const Dims& m) {
   w.dgu = c.take(m.T * 2 * m.I * 2);
   w.dh2 = c.take(m.T * m.H * 2);
   w.partial = c.take(norm_partial_bytes(m));
-  w.kpart_floats = max_kpart_floats({
-      product(ls::EPI_GLU_FWD, true, true, m.T, glu_cols(m), m.H),  // gate/up projection
-      product(ls::EPI_RESID, true, true, m.T, m.H, m.I),            // down projection
-      product(ls::EPI_GLU_BWD, true, false, m.T, m.I, m.H),         // dact
-      product(ls::EPI_BF16, true, false, m.T, m.H, 2 * m.I),        // dh2
-      product(ls::EPI_F32, false, false, m.H, m.I, m.T),            // dWd
-      product(ls::EPI_F32, false, false, 2 * m.I, m.H, m.T),        // dWg/dWu
-  });
+  w.kpart_floats = max_kpart_floats(mlp_products(m));
   w.kpart = c.take((size_t)w.kpart_floats * 4);
   w.total = c.off;
   return w;
@@ -763,11 +774,10 @@ StackWs stack_ws_layout(const ls_stack_cfg& c) {
   w.dxb = k.take(act);
   w.partial = k.take(norm_partial_bytes(m));
   w.dx2 = k.take(act);
-  w.head_kpart_floats = max_kpart_floats({
-      product(ls::EPI_BF16, true, true, logits_rows(c), c.vocab, m.H),   // logits
-      product(ls::EPI_BF16, true, false, logits_rows(c), m.H, c.vocab),  // dh head
-      product(ls::EPI_F32, false, false, c.vocab, m.H, logits_rows(c)),  // dE head
-  });
+  w.head_kpart_floats = max_kpart_floats(
+      std::array<Product, 3>{product("logits", ls::EPI_BF16, true, true, logits_rows(c), c.vocab, m.H),
+                             product("dh head", ls::EPI_BF16, true, false, logits_rows(c), m.H, c.vocab),
+                             product("dE head", ls::EPI_F32, false, false, c.vocab, m.H, logits_rows(c))});
   w.attn = attn_ws_layout(m);
   w.mlp = mlp_ws_layout(m);
   w.scratch = k.take(std::max({w.attn.total, w.mlp.total, (size_t)w.head_kpart_floats * 4}));
@@ -1158,6 +1168,34 @@ int ls_gemm_nn(int64_t M, int64_t N, int64_t K, const ls_bf16* A, const ls_bf16*
 int ls_gemm_tile_override(int32_t bm, int32_t bn) {
   if (ls::gemm_tile_override(bm, bn) != 0) return fail(LS_ERR_SHAPE, "tile sizes must be 256 or 192 (0, 0: automatic)");
   return LS_OK;
+}
+
+// For the tests, and not in ls.h: the tile, the LDS stages of A and the slices
+// of K (out[0..3]: rows, columns, stages, slices) that a product would run with.
+// layout 0, 1, 2: ls_gemm_nt, _nn, _tn, which have no scratch; the other call
+// names a product of a sub-layer by its step's label.
+static void put_plan(const ls::GemmPlan& p, int32_t* out) {
+  out[0] = p.bm;
+  out[1] = p.bn;
+  out[2] = p.stages();
+  out[3] = p.ks;
+}
+int ls_test_gemm_plan(int32_t layout, int64_t M, int64_t N, int64_t K, int32_t* out) {
+  if (int e = check_gemm(M, N, K)) return e;
+  put_plan(ls::gemm_plan(product("", layout == 2 ? ls::EPI_F32 : ls::EPI_BF16, layout != 2, layout == 0, M, N, K).g, 0), out);
+  return LS_OK;
+}
+int ls_test_step_plan(const ls_block_cfg* cfg, const char* label, int32_t* out) {
+  if (int e = check_cfg(cfg)) return e;
+  const Dims m = dims_of(*cfg);
+  const auto attn = attn_products(m), mlp = mlp_products(m);
+  for (const auto* list : {&attn, &mlp})
+    for (const Product& p : *list)
+      if (!strcmp(p.label, label)) {
+        put_plan(ls::gemm_plan(p.g, INT64_MAX), out);
+        return LS_OK;
+      }
+  return fail(LS_ERR_SHAPE, "no product is labelled %s", label);
 }
 
 int ls_gemm_tn(int64_t M, int64_t N, int64_t K, const ls_bf16* A, const ls_bf16* B, float* C, int accumulate,

@@ -158,11 +158,6 @@ std::atomic<int> g_tile_override{0};  // 0: automatic, else 1000 * BM + BN
 // (186 MiB) 1159 against 1396, 4864 x 3400 x 28544 in four (252 MiB) 932 against
 // 1017; 5190 x 3328 x 27264 906 in three (198 MiB), 880 in four (264 MiB), 931
 // unsplit.
-struct Plan {
-  int bm = 256, bn = 256, ks = 1;
-  bool deep = true;  // 128 x 128: four stages, one workgroup per CU
-};
-
 // Slices of K for an fp32 weight-gradient product whose 256 x 256 tiles fill
 // at most half the compute units: as many as fill them, at most 8, each at
 // least 8 k tiles deep.
@@ -180,14 +175,14 @@ int64_t kpart_need(const GemmArgs& a, int ks) {
 }
 
 // forced: 0, or the tile shape of ls_gemm_tile_override (1000 BM + BN).
-Plan make_plan(const GemmArgs& a, int64_t kpart_floats, int forced) {
+GemmPlan make_plan(const GemmArgs& a, int64_t kpart_floats, int forced) {
   const bool nt = a.a_kcontig && a.b_kcontig, f32 = a.epi == EPI_F32;
   // 192-wide tiles of a k-contiguous B put a wave's blocks in two 64-row segments: one buffer only
   const bool n192 = nt ? (a.epi == EPI_BF16 || a.epi == EPI_RESID) && a.b_start[1] >= a.N : a.epi != EPI_GLU_BWD;
   const bool m192 = f32;
   const int ncu = compute_units();
   const int64_t ktiles = ((int64_t)a.K + KT - 1) / KT;
-  Plan best;
+  GemmPlan best;
   if (forced) {
     const int bm = forced / 1000, bn = forced % 1000;
     if ((bm == 256 || m192) && (bn == 256 || n192)) {
@@ -204,7 +199,7 @@ Plan make_plan(const GemmArgs& a, int64_t kpart_floats, int forced) {
     if (kpart_need(a, ks) > std::min(kpart_floats, LLC_BYTES / 4)) return;
     const int64_t wgs = (int64_t)((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn) * ks;
     const double kt = (double)((ktiles + ks - 1) / ks);
-    Plan p;
+    GemmPlan p;
     p.bm = bm;
     p.bn = bn;
     p.ks = ks;
@@ -268,6 +263,10 @@ int64_t gemm_kpart_floats(const GemmArgs& a) {
   return need;
 }
 
+GemmPlan gemm_plan(const GemmArgs& a, int64_t kpart_floats) {
+  return make_plan(a, kpart_floats, g_tile_override.load(std::memory_order_relaxed));
+}
+
 hipError_t gemm(const GemmArgs& args, hipStream_t s) {
   GemmArgs a = args;
   // A k-contiguous B split over buffers (or gate/up interleaved) is loaded a
@@ -275,7 +274,7 @@ hipError_t gemm(const GemmArgs& args, hipStream_t s) {
   if (a.b_kcontig && ((a.b_start[1] % 64 && a.b_start[1] < a.N) || (a.b_start[2] % 64 && a.b_start[2] < a.N)))
     return hipErrorInvalidValue;
   if (!a.a_kcontig && a.b_kcontig) return hipErrorInvalidValue;
-  const Plan p = make_plan(a, a.kpart ? a.kpart_floats : 0, g_tile_override.load(std::memory_order_relaxed));
+  const GemmPlan p = gemm_plan(a, a.kpart ? a.kpart_floats : 0);
   a.ksplit = p.ks;
   a.group_m = group_rows(a.M, a.N, a.K, p.bm, p.bn);
   const GemmTile t = p.bm == 128 ? (p.deep ? TILE_128_DEEP : TILE_128)

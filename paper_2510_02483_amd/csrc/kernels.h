@@ -61,6 +61,14 @@ struct GemmArgs {
   int group_m = 8;  // tile rows per group of the launch order (set by the launch)
 };
 
+// The workgroup tile and the slices of K of a launch.
+struct GemmPlan {
+  int bm = 256, bn = 256, ks = 1;
+  bool deep = true;  // 128 x 128: four LDS stages, one workgroup per CU; else two and two
+  int stages() const { return bn != 128 ? 2 : bm == 256 ? 3 : deep ? 4 : 2; }
+};
+// What gemm() chooses with kpart_floats of scratch (and the forced shape, if any).
+GemmPlan gemm_plan(const GemmArgs& a, int64_t kpart_floats);
 hipError_t gemm(const GemmArgs& a, hipStream_t s);
 // Floats of GemmArgs::kpart with which a product of this shape and epilogue
 // runs with its full split of K (0: it is not split).

@@ -6,6 +6,7 @@ Tolerances (bf16 inputs, bf16 stored intermediates, fp32 accumulation):
 """
 from __future__ import annotations
 
+import ctypes
 import sys
 
 import numpy as np
@@ -13,7 +14,7 @@ import pytest
 import torch
 
 from oracle import block as ob
-from paper_2510_02483_amd import configs
+from paper_2510_02483_amd import configs, lib as L
 
 OUT_TOL = 2e-2
 GRAD_TOL = 3e-2
@@ -50,6 +51,22 @@ def oracle_block(c, f):
     w = {k: f[k] for k in ("wq", "wk", "wv", "wo", "wg", "wu", "wd", "attn_norm", "mlp_norm")}
     return ob.block_fwd_bwd(f["x"], w, f["dy"], n_q_heads=c.n_q_heads, n_kv_heads=c.n_kv_heads,
                             rope_theta=c.rope_theta, eps=c.rms_eps)
+
+
+def gemm_plan(layout, M, N, K):
+    """(tile rows, tile columns, LDS stages, slices of K) that ls_gemm_nt, _nn or _tn (layout 0, 1, 2) runs with."""
+    out = (ctypes.c_int32 * 4)()
+    i64 = ctypes.c_int64
+    assert L.lib().ls_test_gemm_plan(layout, i64(M), i64(N), i64(K), out) == 0
+    return tuple(out)
+
+
+def step_plan(c, label):
+    """The same of one product of a sub-layer, by its step's label."""
+    out = (ctypes.c_int32 * 4)()
+    cfg = L.make_cfg(c)
+    assert L.lib().ls_test_step_plan(ctypes.byref(cfg), label.encode(), out) == 0, label
+    return tuple(out)
 
 
 def bf16_randn(shape, seed, std=1.0, device="cuda"):

@@ -160,6 +160,19 @@ def test_partial_sums_fit_the_last_level_cache(c):
     assert L.ls_query_sizes(c)["mlp_workspace"] <= rest + (256 << 20)
 
 
+def test_shapes_of_the_tile_tests_take_the_kernels_they_name():
+    """The plans that the GPU tests of the narrow tiles and of split K assert, here on the CPU."""
+    import test_gpu_small_tiles as t
+    from gpu_util import gemm_plan, step_plan
+    for layout, kernel, M, N in t.NARROW:
+        for K in t.KS:
+            assert gemm_plan(("nt", "nn", "tn").index(layout), M, N, K) == kernel + (1,), (layout, M, N, K)
+    for _, c, steps in t.INSTANCES:
+        for step, (kernel, split) in steps.items():
+            plan = step_plan(c, step)
+            assert plan[:3] == kernel and (plan[3] > 1) == bool(split), (c.tokens, c.hidden, step, plan)
+
+
 def _stack_args(sc, L_=None):
     """Fake, disjoint, aligned device addresses for every stack argument (the
     checks run before any HIP call, so nothing is dereferenced)."""
