@@ -190,7 +190,7 @@ AttnSaved attn_saved_layout(const Dims& m) {
   s.o = c.take(m.T * m.Pq * 2);
   s.r1 = c.take(m.T * 4);
   s.lse = c.take(m.B * m.nq * m.S * 4);
-  s.rope = c.take(m.S * m.dp * 4);  // cos and sin, S x dp/2 each
+  s.rope = c.take(m.S * m.dp * 4);  // cos and sin, S x dp/2 each; last: a stack's layers share one table and leave it out
   s.total = c.off;
   return s;
 }
@@ -782,7 +782,7 @@ StackWs stack_ws_layout(const ls_stack_cfg& c) {
   w.mlp = mlp_ws_layout(m);
   w.scratch = k.take(std::max({w.attn.total, w.mlp.total, (size_t)w.head_kpart_floats * 4}));
   Carver one;
-  w.asv = one.take(attn_saved_layout(m).total);
+  w.asv = one.take(attn_saved_layout(m).rope);  // up to the table, which is at w.rope
   w.msv = one.take(mlp_saved_layout(m).total);
   w.x2 = one.take(act);
   w.set_stride = one.off;

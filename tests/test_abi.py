@@ -211,6 +211,18 @@ def test_stack_workspace_and_config_checks():
     assert lib.ls_stack_workspace(None, ctypes.byref(n)) == 1
 
 
+@pytest.mark.parametrize("recompute", [False, True])
+def test_stack_holds_one_rope_table(recompute):
+    """The layers of a stack share its RoPE table: a layer adds its input, and without
+    recomputation the saved state of both sub-layers but the table, and its x2."""
+    c = configs.TINY.with_(batch=1, seq=2048)
+    sc = configs.TINY_STACK.with_(block=c, recompute=recompute)
+    grow = L.ls_stack_workspace(sc.with_(n_layers=3)) - L.ls_stack_workspace(sc.with_(n_layers=2))
+    act, s = 2 * c.tokens * c.hidden, L.ls_query_sizes(c)
+    table = 4 * c.seq * c.head_dim
+    assert grow == act + (act if recompute else act + s["attn_saved"] - table + s["mlp_saved"])
+
+
 def test_stack_argument_checks():
     lib = L.lib()
     sc = configs.TINY_STACK
