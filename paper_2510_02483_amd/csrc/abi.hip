@@ -447,10 +447,9 @@ int run_attn_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const 
   return LS_OK;
 }
 
-int run_attn_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x, const ls_block_weights* w,
+int run_attn_bwd(const Dims& m, const bf16_t* x, const ls_block_weights* w,
                  const void* saved, const bf16_t* dx2, bf16_t* dx, const ls_block_grads* gr, int accumulate, void* ws,
                  const AttnWs& wl, const float* rope, hipStream_t st) {
-  (void)cfg;
   const AttnSaved sv = attn_saved_layout(m);
   const bf16_t* h1 = at<bf16_t>(saved, sv.h1);
   const bf16_t* qkv = at<bf16_t>(saved, sv.qkv);
@@ -623,10 +622,9 @@ int run_mlp_fwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x2, const 
   return LS_OK;
 }
 
-int run_mlp_bwd(const ls_block_cfg& cfg, const Dims& m, const bf16_t* x2, const ls_block_weights* w,
+int run_mlp_bwd(const Dims& m, const bf16_t* x2, const ls_block_weights* w,
                 const void* saved, const bf16_t* dy, bf16_t* dx2, const ls_block_grads* gr, int accumulate, void* ws,
                 const MlpWs& wl, hipStream_t st) {
-  (void)cfg;
   const MlpSaved sv = mlp_saved_layout(m);
   const bf16_t* h2 = at<bf16_t>(saved, sv.h2);
   const bf16_t* gu = at<bf16_t>(saved, sv.gu);
@@ -859,7 +857,7 @@ int ls_attn_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weight
   const AttnWs wl = attn_ws_layout(m);
   if (workspace_bytes < wl.total)
     return fail(LS_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, wl.total);
-  return run_attn_bwd(*cfg, m, (const bf16_t*)x, w, attn_saved, (const bf16_t*)dx2, (bf16_t*)dx, g, accumulate != 0,
+  return run_attn_bwd(m, (const bf16_t*)x, w, attn_saved, (const bf16_t*)dx2, (bf16_t*)dx, g, accumulate != 0,
                       workspace, wl, nullptr, (hipStream_t)stream);
 }
 
@@ -896,7 +894,7 @@ int ls_mlp_bwd(const ls_block_cfg* cfg, const ls_bf16* x2, const ls_block_weight
   const MlpWs wl = mlp_ws_layout(m);
   if (workspace_bytes < wl.total)
     return fail(LS_ERR_WORKSPACE, "workspace %zu < %zu bytes", workspace_bytes, wl.total);
-  return run_mlp_bwd(*cfg, m, (const bf16_t*)x2, w, mlp_saved, (const bf16_t*)dy, (bf16_t*)dx2, g, accumulate != 0,
+  return run_mlp_bwd(m, (const bf16_t*)x2, w, mlp_saved, (const bf16_t*)dy, (bf16_t*)dx2, g, accumulate != 0,
                      workspace, wl, (hipStream_t)stream);
 }
 
@@ -925,8 +923,8 @@ int ls_block_fwd_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_w
   if (int e = run_attn_fwd(*cfg, m, (const bf16_t*)x, w, x2, asv, scratch, bl.attn, nullptr, st)) return e;
   if (int e = run_mlp_fwd(*cfg, m, x2, w, (bf16_t*)y, msv, at<float>(scratch, bl.mlp.kpart), bl.mlp.kpart_floats, st))
     return e;
-  if (int e = run_mlp_bwd(*cfg, m, x2, w, msv, (const bf16_t*)dy, dx2, g, acc, scratch, bl.mlp, st)) return e;
-  return run_attn_bwd(*cfg, m, (const bf16_t*)x, w, asv, dx2, (bf16_t*)dx, g, acc, scratch, bl.attn, nullptr, st);
+  if (int e = run_mlp_bwd(m, x2, w, msv, (const bf16_t*)dy, dx2, g, acc, scratch, bl.mlp, st)) return e;
+  return run_attn_bwd(m, (const bf16_t*)x, w, asv, dx2, (bf16_t*)dx, g, acc, scratch, bl.attn, nullptr, st);
 }
 
 int ls_timing_begin(const char* label, int max_launches) {
@@ -1364,9 +1362,9 @@ int ls_stack_fwd_bwd(const ls_stack_cfg* cfg, const int32_t* ids, const int32_t*
                               wl.mlp.kpart_floats, st, true, false))
         return e;
     }
-    if (int e = run_mlp_bwd(bc, m, x2, &w->layers[l], sv + wl.msv, dcur, dx2, &g->layers[l], acc, scratch, wl.mlp, st))
+    if (int e = run_mlp_bwd(m, x2, &w->layers[l], sv + wl.msv, dcur, dx2, &g->layers[l], acc, scratch, wl.mlp, st))
       return e;
-    if (int e = run_attn_bwd(bc, m, xs(l), &w->layers[l], sv + wl.asv, dx2, dnext, &g->layers[l], acc, scratch, wl.attn,
+    if (int e = run_attn_bwd(m, xs(l), &w->layers[l], sv + wl.asv, dx2, dnext, &g->layers[l], acc, scratch, wl.attn,
                              rope, st))
       return e;
     std::swap(dcur, dnext);
