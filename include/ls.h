@@ -30,7 +30,9 @@
  *   - Pointers: every pointer argument is device memory owned by the caller,
  *     16-byte aligned, dense (no strides).  The library keeps no reference to
  *     any of them after a call returns and allocates no device memory in any
- *     call below; scratch space comes from the caller's workspace.
+ *     call below; scratch space comes from the caller's workspace.  A call may
+ *     write all of a workspace that it is given, forward passes too: calls
+ *     that may run at the same time need one each.
  *   - Streams: `stream` is a hipStream_t (NULL = the null stream).  Calls only
  *     enqueue work and return; device faults surface at the caller's next
  *     synchronisation.  No host synchronisation happens inside a call.
@@ -111,7 +113,8 @@ typedef struct {
   size_t block_workspace;/* scratch for ls_block_fwd_bwd (includes both saved states) */
 } ls_sizes;
 
-/* Fill *out with the buffer sizes the calls below need for *cfg. */
+/* Fill *out with the buffer sizes the calls below need for *cfg (whatever tile
+ * shape ls_gemm_tile_override forces). */
 int ls_query_sizes(const ls_block_cfg* cfg, ls_sizes* out);
 
 /* Attention sub-layer forward (Section 2.4: RMSNorm, RoPE, causal GQA):
@@ -141,8 +144,9 @@ int ls_attn_bwd(const ls_block_cfg* cfg, const ls_bf16* x, const ls_block_weight
 /* MLP sub-layer forward (Section 2.4: RMSNorm, SwiGLU):
  *   y = x2 + (silu(h2 Wg^T) * (h2 Wu^T)) Wd^T,  h2 = RMSNorm(x2; mlp_norm).
  * mlp_saved: opaque, mlp_saved bytes (h2, gate and up outputs, their product,
- * the RMSNorm scales).  workspace: of mlp_workspace bytes it lets products of few
- * tokens split K (partial sums are written there); NULL or less is accepted too. */
+ * the RMSNorm scales).  workspace: with mlp_workspace bytes, products of few
+ * tokens split K (partial sums are written there); NULL or less is accepted
+ * too and leaves them unsplit. */
 int ls_mlp_fwd(const ls_block_cfg* cfg, const ls_bf16* x2, const ls_block_weights* w,
                ls_bf16* y, void* mlp_saved, void* workspace, size_t workspace_bytes,
                void* stream);

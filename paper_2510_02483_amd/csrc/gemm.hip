@@ -31,8 +31,8 @@ __global__ __launch_bounds__(256) void kpart_reduce_kernel(GemmArgs p) {
 // sums ([slice][M][N]) are added in slice order and go through the product's
 // epilogue.  A thread takes 8 columns of a row (and their partner columns: the
 // other half of the head, the up feature).  Bound by memory: reads ksplit M N
-// fp32 values, most of them still in the last-level cache (25 MB for 2 slices
-// of 504 x 3072: 5 us).
+// fp32 values, at most the last-level cache's size (make_plan) and most of them
+// still in it (12.4 MB for 2 slices of 504 x 3072: 5 us).
 LS_DEV void sum_slices8(const GemmArgs& p, int m, int n, float v[8]) {
   const float* src = p.kpart + (int64_t)m * p.N + n;
   const int64_t per = (int64_t)p.M * p.N;
@@ -141,23 +141,35 @@ std::atomic<int> g_tile_override{0};  // 0: automatic, else 1000 * BM + BN
 //   256 x 256        1.3 per k tile with the chip full (1.05 with a quarter of it), fixed 9
 //   narrower sides   proportional to the area, 10% more per 192-wide side (more LDS traffic per flop),
 //                    3% for 192 columns with a k-contiguous A (whose B has a third LDS stage)
+//   256 x 128        one workgroup per CU, three stages: 0.85 per k tile full, 0.45 with few
+//                    workgroups, fixed 6; 8% more with a k-strided operand
 //   128 x 128        one workgroup per CU, four LDS stages: 0.49 per k tile full, 0.34 at a third
 //                    of the chip, fixed 4.5; two per CU with two stages (more tiles than CUs):
 //                    0.97 per k tile of the pair, fixed 6; 12% more with a k-strided operand
 //   finishing a split  4.5 and its partial sums written and read back at 2.5 TB/s
+// What is about the same for every candidate is left out: the estimate ranks
+// them and is no prediction.  Large launches take longer, most of all those whose
+// epilogue moves much (SwiGLU backward reads 2 M N saved values and writes as
+// many): 8192 x 3072 x 16384 NN 532 estimated, 628 measured; 8192 x 8192 x 3072
+// with the SwiGLU backward 286 and 430.
+//
 // Measured with these choices against 256 x 256 or 256 x 192 alone: 2048 x 2048
 // x 22016 327 -> 169 us (256 workgroups where there were 88), 504 x 3072 x 8192
 // 106 -> 37 us (two slices), 2048 x 2560 x 2048 36 -> 28 us, 256 x 512 x 256
 // 10 -> 6 us; 8192 x 16384 x 3072 stays 256 x 256 (620 us against 760 with 128 x 128).
 //
-// Partial sums are held to the size of the last-level cache.  They are the
-// caller's workspace, and beyond the cache they go to memory and back, which
-// leaves little of the gain: 8192 x 6656 x 35840 in three slices (624 MiB,
-// doubling the MLP's workspace) 3317 us against 3410 unsplit, 4096 rows of it
-// (312 MiB) 1560 against 1648.  Within it: 9536 x 2560 x 24816 in two slices
-// (186 MiB) 1159 against 1396, 4864 x 3400 x 28544 in four (252 MiB) 932 against
-// 1017; 5190 x 3328 x 27264 906 in three (198 MiB), 880 in four (264 MiB), 931
-// unsplit.
+// Grids of more than one round are split as well where that leaves less of the
+// last round empty.  Partial sums are held to the size of the last-level cache.
+// They are the caller's workspace, and beyond the cache they go to memory and
+// back, which leaves little of the gain: 8192 x 6656 x 35840 in three slices (624
+// MiB, doubling the MLP's workspace) 3317 us against 3410 unsplit, 4096 rows of it
+// (312 MiB) 1560 against 1648.  Within it: 9536 x 2560 x 24816 in two slices (186
+// MiB) 1159 against 1396, 4864 x 3400 x 28544 in four (252 MiB) 932 against 1017,
+// 12288 x 2048 x 17888 in two (192 MiB) 845 against 957; 432 x 40128 x 8192 with
+// the SwiGLU backward in two (132 MiB) 356 against 422 and 128 x 67200 x 6656 with
+// the forward (66 MiB) 317 against 325; 5190 x 3328 x 27264 906 in three (198
+// MiB), 880 in four (264 MiB), 931 unsplit.
+
 // Slices of K for an fp32 weight-gradient product whose 256 x 256 tiles fill
 // at most half the compute units: as many as fill them, at most 8, each at
 // least 8 k tiles deep.

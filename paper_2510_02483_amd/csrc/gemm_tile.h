@@ -498,7 +498,8 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_kernel(GemmArgs p) {
       kc_setup(lb, (rb >> 6) & 1 ? p.B[1] : p.B[0], (rb >> 7) * 64, p.glu_rows, p.ldb, lane, wave * NB);
     } else {
       // row segments start at multiples of 64; a wave's blocks lie in one of them
-      // when B is split (256-wide tiles), or span two of a single buffer
+      // when B may be split (256- and 128-wide tiles), or span two of a single
+      // buffer (192-wide ones)
       const int sg = rb >= p.b_start[2] ? 2 : (rb >= p.b_start[1] ? 1 : 0);
       const int st = sg == 2 ? p.b_start[2] : (sg == 1 ? p.b_start[1] : 0);
       const int en = min(p.N, sg == 2 ? p.N : (sg == 1 ? p.b_start[2] : p.b_start[1]));
@@ -1030,7 +1031,7 @@ constexpr int waves_of() {
 // Stages of B: three beside two of A for the 256 x 192 tiles of the products
 // with a k-contiguous A (138 KB of LDS).  With two, the loads of a tile had to
 // go out in the first half of a period and were still waited for: 8192 x 3072 x
-// 16384 NN 690 -> 633 us, 8192 x 3072 x 8192 NT 292 -> 286 us.  256 x 256 tiles
+// 16384 NN 690 -> 633 us, 8192 x 3072 x 8192 NT 302 -> 295 us.  256 x 256 tiles
 // have no LDS for it, and the weight-gradient (TN) products are no faster
 // (326 -> 330 us for 3072 x 8192 x 8192).
 template <bool AK, int BM, int BN>

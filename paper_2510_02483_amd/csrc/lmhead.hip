@@ -2,7 +2,8 @@
 // cross-entropy over rows of vocabulary logits, with its gradient written in
 // place of the logits.
 //
-// All of these are bound by HBM bandwidth.  A cross-entropy row of V bf16
+// The embedding kernels are bound by HBM bandwidth, the cross-entropy by the
+// vector instructions between its loads and its stores.  A row of V bf16
 // logits is read once into the registers of one 1024-thread workgroup (up to
 // 131072 entries; 16 bytes per thread and step), reduced to its max and
 // sum-exp, and overwritten once with the gradient; larger vocabularies stream

@@ -15,8 +15,7 @@ from gpu_util import GRAD_TOL, OUT_TOL, bf16_randn, f64, fro_rel, max_rel, need_
 pytestmark = pytest.mark.gpu
 
 # the 4104 x 4200 shape has more output tiles than compute units (17 x 17 and
-# more), so its products run persistent: workgroups walk several tiles, ragged
-# ones included.  K takes ragged tile counts (the masked loop) and whole ones of
+# more), so its products take more than one round of workgroups.  K takes ragged tile counts (the masked loop) and whole ones of
 # 1, 2, 3, 9 and 10 tiles of 64 (the unmasked loop, which with one wave per SIMD
 # runs two tiles per pass: an odd count leaves one tile for the masked loop).
 GEMM_SHAPES = [(136, 264, 72), (520, 776, 1000), (256, 512, 640), (8, 8, 8), (1032, 264, 1376), (392, 584, 200),
